@@ -320,7 +320,7 @@ __device__ __forceinline__ uint32_t lpr_sum_column(const uint32_t* col, int stri
     if constexpr (DT == kDtF32)
         return __float_as_uint(lo);
     else
-        return f32_to_bf16(lo) | (f32_to_bf16(hi) << 16);
+        return f32_to_bf16x2(lo, hi);
 }
 
 template <int PT, int DT>
@@ -724,7 +724,7 @@ hipError_t launch_allreduce(const void* const* in, void* const* out, int P, size
     const int gsize = dest_groups > 1 ? dest_groups : 1;
     s.dpi = P / gsize;
     int nt, vpt;
-    pick_ar_shape(s.nvec, P, nt, vpt);
+    pick_ar_shape(s.nvec, P, dtype, nt, vpt);
     if (vpt == 8 && P != 2 && P != 4 && P != 8) return hipErrorInvalidValue;
     const int64_t cv = static_cast<int64_t>(nt) * vpt;
     const int64_t groups = (s.nvec + cv - 1) / cv;
@@ -816,7 +816,7 @@ hipError_t launch_two_shot_fused(const void* const* in, void* const* out, int P,
     const int64_t nvec = static_cast<int64_t>(bytes / 16);
     const int64_t mv = nvec / P;
     int nt, vpt;
-    pick_ar_shape(nvec, P, nt, vpt);
+    pick_ar_shape(nvec, P, dtype, nt, vpt);
     if (vpt == 8 && P == 16) vpt = 4;
     const int64_t cv = static_cast<int64_t>(nt) * vpt;
     const int64_t wcs = (mv + cv - 1) / cv;

@@ -177,14 +177,48 @@ inline void pick_ag_shape(int64_t out_vectors, int P, int& nt, int& vpt) {
 // 2, 4 or 8 ranks a forced 8 vectors per thread is kept (other rank counts
 // have no such kernel and get 4).
 //
+// Sizes of a few MiB per rank with 2, 4, 8 and 16 ranks have shapes of their
+// own, by quarter MiB per rank and dtype.  What decides there is how full the
+// rounds of resident workgroups are: a thread holds 16 B x ranks x vectors in
+// registers, so the launch runs in rounds of a size that the shape fixes, and
+// a mostly empty last round, or fewer waves than SIMDs, costs 10-25 %.
+// One-wave workgroups of 8 vectors make the rounds short to fill and keep
+// 8 KiB of each buffer contiguous.  us per call in graphs on MI355X, shared
+// rule -> shape taken (3 buffer sets in turn):
+//   2 ranks bf16   4 MiB 4.16 -> 3.33 (64x8),      8 MiB 5.9 -> 5.6,    16 MiB 12.6 -> 11.4
+//   4 ranks f32    4 MiB 5.79 -> 5.20 (64x8),      8 MiB 12.0 -> 10.4,  16 MiB 24.6 -> 23.5
+//   8 ranks f32    3 MiB 9.7 -> 8.2 (64x4),        4 MiB 12.1 -> 10.7 (64x8),  7 MiB 23.2 -> 19.5 (256x8)
+//   8 ranks bf16   3 MiB 9.3 -> 8.0 (128x2),       4 MiB 11.0 -> 10.5 (64x8), 12 MiB 37.3 -> 34.6 (64x4)
+//   16 ranks bf16  1.5 MiB 10.2 -> 8.7 (256x2),    2.5 MiB 17.3 -> 13.6 (64x2), 3.5 MiB 23.8 -> 19.7 (64x4)
+// Each row begins where it stopped losing (2 ranks of f32 at 3.25 MiB: 64x8
+// 3.4 against 2.9 us; 4 ranks of bf16 at 3.25-3.75 MiB: 256x2 5.1-5.6 us, 64x8
+// 5.6-6.1, the shared 256x1 5.9-6.6).
+struct ShapeRow {
+    int32_t from;  // quarter MiB per rank from which the row holds
+    int32_t nt, vpt;  // 0: the shared rule
+};
+
+template <int N>
+void ar_row_shape(const ShapeRow (&rows)[N], int64_t vectors_per_rank, int& nt, int& vpt) {
+    constexpr int64_t kQuarter = int64_t(1) << 14;  // vectors in a quarter MiB
+    const ShapeRow* hit = nullptr;
+    for (const ShapeRow& r : rows)
+        if (r.from * kQuarter <= vectors_per_rank) hit = &r;
+    if (hit && hit->nt > 0) {
+        nt = hit->nt;
+        vpt = hit->vpt;
+    }
+}
+
 // 8 ranks, 8-32 MiB per rank: 8 vectors per thread in 256-thread workgroups.
 // That kernel holds 256 VGPRs, so one workgroup per CU runs at a time and
 // the launch proceeds in rounds of 256 workgroups, each moving 32 KiB
-// contiguous per rank buffer.  Measured on MI355X (bf16, cold) it was 5-8 %
-// faster than the shared rule at 8 and 16 MiB per rank, when its chunks fill
-// whole rounds; with a partly empty last round it lost, so it is taken only
-// when the last round is at least 90 % full.
-inline void pick_ar_shape(int64_t vectors_per_rank, int P, int& nt, int& vpt) {
+// contiguous per rank buffer.  Measured on MI355X it was 5-8 % faster than
+// the shared rule at 8 and 16 MiB per rank, when its chunks fill whole
+// rounds, and 5-13 % at 13 MiB, where they fill 81 %; with an emptier last
+// round it lost, and at 20 MiB (83 % full) it was 2 % slower.  So it is taken
+// when the rounds are at least 80 % full, from 16 MiB at least 90 %.
+inline void pick_ar_shape(int64_t vectors_per_rank, int P, int dtype, int& nt, int& vpt) {
     nt = pick_threads(vectors_per_rank, P);
     vpt = pick_vpt(vectors_per_rank, P);
     const bool eight_ok = P == 2 || P == 4 || P == 8;
@@ -192,17 +226,36 @@ inline void pick_ar_shape(int64_t vectors_per_rank, int P, int& nt, int& vpt) {
         vpt = 8;
         return;
     }
-    if (P != 8 || tuning().wg_threads || tuning().vpt) return;
-    if (vectors_per_rank < (int64_t(1) << 19) || vectors_per_rank > (int64_t(1) << 21)) return;
+    if (tuning().wg_threads || tuning().vpt) return;
+    const bool f32 = dtype == kDtF32;
+    static constexpr ShapeRow k2f[] = {{16, 64, 8}, {128, 0, 0}};
+    static constexpr ShapeRow k2b[] = {{13, 64, 8}, {128, 0, 0}};
+    static constexpr ShapeRow k4f[] = {{13, 64, 8}, {80, 0, 0}};
+    static constexpr ShapeRow k4b[] = {{13, 256, 2}, {16, 128, 4}, {20, 64, 8}, {90, 0, 0}};
+    static constexpr ShapeRow k8f[] = {{9, 64, 4}, {13, 64, 8}, {26, 256, 8}, {33, 64, 4}, {64, 0, 0}};
+    static constexpr ShapeRow k8b[] = {{9, 128, 2}, {13, 64, 8}, {26, 256, 8}, {33, 64, 4}, {64, 0, 0}};
+    static constexpr ShapeRow k16f[] = {{5, 256, 2}, {9, 64, 4}, {15, 0, 0}, {20, 128, 2}, {26, 0, 0}, {34, 128, 2},
+                                        {64, 0, 0}};
+    static constexpr ShapeRow k16b[] = {{5, 256, 2}, {9, 64, 2}, {13, 64, 4}, {15, 0, 0}, {20, 128, 2}, {26, 0, 0},
+                                        {34, 128, 2}, {64, 0, 0}};
+    switch (P) {
+        case 2: f32 ? ar_row_shape(k2f, vectors_per_rank, nt, vpt) : ar_row_shape(k2b, vectors_per_rank, nt, vpt); break;
+        case 4: f32 ? ar_row_shape(k4f, vectors_per_rank, nt, vpt) : ar_row_shape(k4b, vectors_per_rank, nt, vpt); break;
+        case 8: f32 ? ar_row_shape(k8f, vectors_per_rank, nt, vpt) : ar_row_shape(k8b, vectors_per_rank, nt, vpt); break;
+        case 16:
+            f32 ? ar_row_shape(k16f, vectors_per_rank, nt, vpt) : ar_row_shape(k16b, vectors_per_rank, nt, vpt);
+            break;
+        default: break;
+    }
+    if (P != 8 || vectors_per_rank <= (int64_t(1) << 19) || vectors_per_rank > (int64_t(1) << 21)) return;
     constexpr int64_t kChunk = 256 * 8, kRound = 256;
     const int64_t G = (vectors_per_rank + kChunk - 1) / kChunk;
     const int64_t rounds = (G + kRound - 1) / kRound;
-    if (G * 10 >= rounds * kRound * 9) {
+    if (G * 10 >= rounds * kRound * (vectors_per_rank < (int64_t(1) << 20) ? 8 : 9)) {
         nt = 256;
         vpt = 8;
     }
 }
-
 
 }  // namespace
 }  // namespace nuna
