@@ -148,7 +148,18 @@ Ptrs<MAXP> make_ptrs(const void* const* in, void* const* out, int nin, int nout)
     return p;
 }
 
-// Direct kernels with 2, 4 or 8 ranks: one use of every rank pointer and of
+// Rank count of a kernel, its first template parameter PT:
+//   PT > 0  exactly PT ranks, known at compile time;
+//   PT < 0  a run-time count of at most -PT ranks, whose pointers still sit at
+//           compile-time offsets of the arguments (a wave-uniform test skips
+//           the missing ranks);
+//   PT = 0  a run-time count of up to 64 ranks, through the rank table.
+template <int PT>
+constexpr int rank_cap() {
+    return PT < 0 ? -PT : PT;
+}
+
+// Direct kernels with up to 8 pointer slots: one use of every rank pointer and of
 // the given scalar arguments in a single statement, so that the kernel's
 // first round of scalar loads brings all of them.  Without it the compiler
 // loads a pointer where it is first used: a chain of argument loads behind
@@ -163,46 +174,70 @@ Ptrs<MAXP> make_ptrs(const void* const* in, void* const* out, int nin, int nout)
     "s"(p.in[0]), "s"(p.in[1]), "s"(p.in[2]), "s"(p.in[3]), "s"(p.out[0]), "s"(p.out[1]), "s"(p.out[2]), "s"(p.out[3])
 #define NUNA_PIN_PTRS2(p) "s"(p.in[0]), "s"(p.in[1]), "s"(p.out[0]), "s"(p.out[1])
 
-template <int PT, class A, class B, class C>
-__device__ __forceinline__ void pin_args(const Ptrs<PT>& p, A a, B b, C c) {
-    if constexpr (PT == 8)
+template <int N, class A, class B, class C>
+__device__ __forceinline__ void pin_args(const Ptrs<N>& p, A a, B b, C c) {
+    if constexpr (N == 8)
         asm volatile("" ::NUNA_PIN_PTRS8(p), "s"(a), "s"(b), "s"(c));
-    else if constexpr (PT == 4)
+    else if constexpr (N == 4)
         asm volatile("" ::NUNA_PIN_PTRS4(p), "s"(a), "s"(b), "s"(c));
-    else if constexpr (PT == 2)
+    else if constexpr (N == 2)
         asm volatile("" ::NUNA_PIN_PTRS2(p), "s"(a), "s"(b), "s"(c));
     else
         asm volatile("" ::"s"(a), "s"(b), "s"(c));
 }
 
-template <int PT, class A, class B, class C, class D, class E, class F>
-__device__ __forceinline__ void pin_args(const Ptrs<PT>& p, A a, B b, C c, D d, E e, F f) {
-    if constexpr (PT == 8)
+template <int N, class A, class B, class C, class D>
+__device__ __forceinline__ void pin_args(const Ptrs<N>& p, A a, B b, C c, D d) {
+    if constexpr (N == 8)
+        asm volatile("" ::NUNA_PIN_PTRS8(p), "s"(a), "s"(b), "s"(c), "s"(d));
+    else if constexpr (N == 4)
+        asm volatile("" ::NUNA_PIN_PTRS4(p), "s"(a), "s"(b), "s"(c), "s"(d));
+    else if constexpr (N == 2)
+        asm volatile("" ::NUNA_PIN_PTRS2(p), "s"(a), "s"(b), "s"(c), "s"(d));
+    else
+        asm volatile("" ::"s"(a), "s"(b), "s"(c), "s"(d));
+}
+
+template <int N, class A, class B, class C, class D, class E, class F>
+__device__ __forceinline__ void pin_args(const Ptrs<N>& p, A a, B b, C c, D d, E e, F f) {
+    if constexpr (N == 8)
         asm volatile("" ::NUNA_PIN_PTRS8(p), "s"(a), "s"(b), "s"(c), "s"(d), "s"(e), "s"(f));
-    else if constexpr (PT == 4)
+    else if constexpr (N == 4)
         asm volatile("" ::NUNA_PIN_PTRS4(p), "s"(a), "s"(b), "s"(c), "s"(d), "s"(e), "s"(f));
-    else if constexpr (PT == 2)
+    else if constexpr (N == 2)
         asm volatile("" ::NUNA_PIN_PTRS2(p), "s"(a), "s"(b), "s"(c), "s"(d), "s"(e), "s"(f));
     else
         asm volatile("" ::"s"(a), "s"(b), "s"(c), "s"(d), "s"(e), "s"(f));
 }
 
+template <int N, class A, class B, class C, class D, class E, class F, class G>
+__device__ __forceinline__ void pin_args(const Ptrs<N>& p, A a, B b, C c, D d, E e, F f, G g) {
+    if constexpr (N == 8)
+        asm volatile("" ::NUNA_PIN_PTRS8(p), "s"(a), "s"(b), "s"(c), "s"(d), "s"(e), "s"(f), "s"(g));
+    else if constexpr (N == 4)
+        asm volatile("" ::NUNA_PIN_PTRS4(p), "s"(a), "s"(b), "s"(c), "s"(d), "s"(e), "s"(f), "s"(g));
+    else if constexpr (N == 2)
+        asm volatile("" ::NUNA_PIN_PTRS2(p), "s"(a), "s"(b), "s"(c), "s"(d), "s"(e), "s"(f), "s"(g));
+    else
+        asm volatile("" ::"s"(a), "s"(b), "s"(c), "s"(d), "s"(e), "s"(f), "s"(g));
+}
+
 // Rank r's pointer for a uniform run-time r, chosen among the pointers
 // already in SGPRs (a chain of scalar selects) instead of a scalar load from
 // the argument segment.
-template <int PT>
-__device__ __forceinline__ const uint4* in_at(const Ptrs<PT>& p, int r) {
+template <int N>
+__device__ __forceinline__ const uint4* in_at(const Ptrs<N>& p, int r) {
     const uint4* x = p.in[0];
 #pragma unroll
-    for (int q = 1; q < PT; ++q) x = r == q ? p.in[q] : x;
+    for (int q = 1; q < N; ++q) x = r == q ? p.in[q] : x;
     return x;
 }
 
-template <int PT>
-__device__ __forceinline__ uint4* out_at(const Ptrs<PT>& p, int r) {
+template <int N>
+__device__ __forceinline__ uint4* out_at(const Ptrs<N>& p, int r) {
     uint4* x = p.out[0];
 #pragma unroll
-    for (int q = 1; q < PT; ++q) x = r == q ? p.out[q] : x;
+    for (int q = 1; q < N; ++q) x = r == q ? p.out[q] : x;
     return x;
 }
 
@@ -286,7 +321,7 @@ __device__ __forceinline__ uint4* out_ptr(const Ptrs<MAXP>& p, const RankTable& 
 // batches of 16.
 template <int PT>
 constexpr int rank_batch() {
-    return PT == 0 ? 16 : PT;
+    return PT == 0 ? 16 : rank_cap<PT>();
 }
 
 // A thread's vectors within a chunk are v0 + j*nt, j < VPT, where nt is the
@@ -363,23 +398,23 @@ __device__ __forceinline__ void reduce_ranks(const Ptrs<MAXP>& p, const RankTabl
                                              int nt, int64_t limit, float (&acc)[VPT][Arith<DT>::kLanes]) {
     using A = Arith<DT>;
     constexpr int B = rank_batch<PT>();
-    if constexpr (PT > 0) {
+    if constexpr (PT != 0) {
+        uint4 buf[B][VPT];
 #pragma unroll
-        for (int r0 = 0; r0 < PT; r0 += B) {
-            uint4 buf[B][VPT];
+        for (int q = 0; q < B; ++q)
+            if (PT > 0 || q < P)
+                load_vecs<FULL, VPT, NT>(buf[q], in_ptr<PT>(p, tab, q) + base, v0, nt, limit);
 #pragma unroll
-            for (int q = 0; q < B; ++q)
-                load_vecs<FULL, VPT, NT>(buf[q], in_ptr<PT>(p, tab, r0 + q) + base, v0, nt, limit);
-#pragma unroll
-            for (int q = 0; q < B; ++q)
+        for (int q = 0; q < B; ++q)
+            if (PT > 0 || q < P) {
 #pragma unroll
                 for (int j = 0; j < VPT; ++j) {
-                    if (r0 + q == 0)
+                    if (q == 0)
                         A::init(acc[j], buf[q][j]);
                     else
                         A::add(acc[j], buf[q][j]);
                 }
-        }
+            }
     } else {
         // Runtime P: batches of B ranks; the last batch may be partial.
         for (int r0 = 0; r0 < P; r0 += B) {

@@ -15,13 +15,16 @@ constexpr int kDtBf16 = 1;
 
 inline size_t dtype_size(int dt) { return dt == kDtF32 ? 4u : 2u; }
 
+// Default rank count from which the many-rank all-reduce kernels run.
+constexpr int kManyRanks = 16;
+
 // Tunables (read once from the environment by the host API; they change the
 // launch shape only, never the arithmetic).
 struct Tuning {
     int max_grid = 0;      // cap on workgroups per launch (persistent loop beyond); 0: 16384
     int wg_threads = 0;    // workgroup size for the streaming kernels (0 = by size)
     int vpt = 0;           // vectors per thread per work item (0 = by size; 8: one-shot all-reduce only)
-    int lpr_min_ranks = 16;           // many-rank all-reduce kernels (tile, lane per rank) from this many ranks
+    int lpr_min_ranks = kManyRanks;   // many-rank all-reduce kernels (tile, lane per rank) from this many ranks
     int64_t lpr_max_vectors = 0;       // lane-per-rank all-reduce up to this many input vectors in total (0: off)
     int combine_vpt = 0;               // combine vectors per thread per pass (0 = default)
     int combine_chunks = 0;            // combine column chunks per token (0 = by size)

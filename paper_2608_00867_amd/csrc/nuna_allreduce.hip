@@ -38,15 +38,17 @@ __device__ __forceinline__ void allreduce_chunk(const Ptrs<MAXP>& p, const RankT
     uint4 y[VPT];
 #pragma unroll
     for (int j = 0; j < VPT; ++j) y[j] = A::narrow(acc[j]);
-    if (PT > 0 && all_dests) {
+    if (PT != 0 && all_dests) {
 #pragma unroll
-        for (int d = 0; d < (PT > 0 ? PT : 1); ++d) {
-            if (d > 0) store_gap(s.gap);
-            if constexpr (WT)
-                store_vecs_wt<FULL, VPT>(out_ptr<PT>(p, tab, d) + cbase, y, static_cast<int>(threadIdx.x), nt,
-                                         s.nvec - cbase);
-            else
-                store_vecs<FULL, VPT>(out_ptr<PT>(p, tab, d), y, v0, nt, s.nvec);
+        for (int d = 0; d < (PT != 0 ? rank_cap<PT>() : 1); ++d) {
+            if (PT > 0 || d < P) {
+                if (d > 0) store_gap(s.gap);
+                if constexpr (WT)
+                    store_vecs_wt<FULL, VPT>(out_ptr<PT>(p, tab, d) + cbase, y, static_cast<int>(threadIdx.x), nt,
+                                             s.nvec - cbase);
+                else
+                    store_vecs<FULL, VPT>(out_ptr<PT>(p, tab, d), y, v0, nt, s.nvec);
+            }
         }
     } else {
         const int d0 = g * s.dpi;
@@ -116,11 +118,22 @@ __global__ __launch_bounds__(kWG) void k_allreduce(Ptrs<MAXP> p, ArShape s, Plac
 // at once.  The general kernel above first reads its placement state and then
 // the pointers, a chain of dependent argument loads that measured about 1 us
 // per launch at 1 MiB per rank on MI355X (5.3 against 4.2 us).
+//
+// Rank counts other than 2, 4, 8 and 16 run it with PT = -4, -8 or -16 (ranks
+// up to 4, 8, 16; `ranks` gives the count).  They used to run the general
+// kernel through the rank table with batches of 16 ranks, whose registers are
+// sized for 16: one wave per SIMD at 4 vectors per thread, and one more
+// dependent load at the start.
 template <int PT, int DT, int VPT, bool WT>
-__global__ __launch_bounds__(kWG) void k_allreduce_direct(Ptrs<PT> p, int64_t nvec, int32_t tail, int32_t gshift,
-                                                          int64_t nitems, int32_t gap) {
+__global__ __launch_bounds__(kWG) void k_allreduce_direct(Ptrs<rank_cap<PT>()> p, int64_t nvec, int32_t tail,
+                                                          int32_t gshift, int64_t nitems, int32_t gap,
+                                                          int32_t ranks) {
     using A = Arith<DT>;
-    pin_args(p, nvec, tail, gshift, nitems, gap, blockDim.x);
+    if constexpr (PT > 0)
+        pin_args(p, nvec, tail, gshift, nitems, gap, blockDim.x);
+    else
+        pin_args(p, nvec, tail, gshift, nitems, gap, blockDim.x, ranks);
+    const int P = PT > 0 ? PT : ranks;
     const int nt = blockDim.x;
     const int64_t cv = static_cast<int64_t>(nt) * VPT;
     const int64_t c = page_item(blockIdx.x, gshift);
@@ -128,19 +141,19 @@ __global__ __launch_bounds__(kWG) void k_allreduce_direct(Ptrs<PT> p, int64_t nv
     const int64_t v0 = c * cv + threadIdx.x;
     ArShape s{};
     s.nvec = nvec;
-    s.dpi = PT;
-    s.P = PT;
+    s.dpi = P;
+    s.P = P;
     s.gap = gap;
-    const RankTable tab{0u, 0u, 0u, 0u};  // compile-time rank count: pointers come from the arguments
+    const RankTable tab{0u, 0u, 0u, 0u};  // pointers come from the arguments
     if ((c + 1) * cv <= nvec)
-        allreduce_chunk<PT, DT, VPT, true, true, WT>(p, tab, s, PT, v0, nt, 0, true, c * cv);
+        allreduce_chunk<PT, DT, VPT, true, true, WT>(p, tab, s, P, v0, nt, 0, true, c * cv);
     else
-        allreduce_chunk<PT, DT, VPT, false, true, WT>(p, tab, s, PT, v0, nt, 0, true, c * cv);
+        allreduce_chunk<PT, DT, VPT, false, true, WT>(p, tab, s, P, v0, nt, 0, true, c * cv);
     if (tail > 0 && blockIdx.x == 0 && static_cast<int>(threadIdx.x) < tail) {
         const int64_t i = nvec * (16 / A::kEsize) + threadIdx.x;
         float a = A::load1(p.in[0], i);
-        for (int r = 1; r < PT; ++r) a = a + A::load1(p.in[r], i);
-        for (int d = 0; d < PT; ++d) A::store1(p.out[d], i, a);
+        for (int r = 1; r < P; ++r) a = a + A::load1(p.in[r], i);
+        for (int d = 0; d < P; ++d) A::store1(p.out[d], i, a);
     }
 }
 
@@ -535,12 +548,12 @@ void launch_ar_p(const void* const* in, void* const* out, int P, const ArShape& 
 template <int PT, int DT, int VPT, bool WT = false>
 void launch_ar_direct_t(const void* const* in, void* const* out, const ArShape& s, const DirectMap& m, int nt,
                         hipStream_t st) {
-    const Ptrs<PT> p = make_ptrs<PT>(in, out, PT, PT);
+    const auto p = make_ptrs<rank_cap<PT>()>(in, out, s.P, s.P);
     hipLaunchKernelGGL((k_allreduce_direct<PT, DT, VPT, WT>), dim3(static_cast<unsigned>(m.grid)), dim3(nt), 0, st, p,
-                       s.nvec, s.tail, m.gshift, m.items, s.gap);
+                       s.nvec, s.tail, m.gshift, m.items, s.gap, s.P);
 }
 
-// Direct kernel for 2, 4, 8 or 16 ranks (8 vectors per thread: 2, 4 or 8 ranks);
+// Direct kernel for up to 16 ranks (8 vectors per thread: 2, 4 or 8 ranks);
 // write-through stores with 8 ranks when `wt`.
 template <int DT, int VPT>
 void launch_ar_direct_p(const void* const* in, void* const* out, int P, const ArShape& s, const DirectMap& m, int nt,
@@ -553,7 +566,12 @@ void launch_ar_direct_p(const void* const* in, void* const* out, int P, const Ar
             else launch_ar_direct_t<8, DT, VPT, false>(in, out, s, m, nt, st);
             break;
         default:
-            if constexpr (VPT != 8) launch_ar_direct_t<16, DT, VPT>(in, out, s, m, nt, st);
+            if constexpr (VPT != 8) {
+                if (P == 16) launch_ar_direct_t<16, DT, VPT>(in, out, s, m, nt, st);
+                else if (P < 4) launch_ar_direct_t<-4, DT, VPT>(in, out, s, m, nt, st);
+                else if (P < 8) launch_ar_direct_t<-8, DT, VPT>(in, out, s, m, nt, st);
+                else launch_ar_direct_t<-16, DT, VPT>(in, out, s, m, nt, st);
+            }
             break;
     }
 }
@@ -709,7 +727,11 @@ hipError_t launch_allreduce(const void* const* in, void* const* out, int P, size
     // below the one-shot kernel at 64 ranks and below the lane-per-rank kernel
     // at every size; beyond that the one-shot kernel's long per-thread streams
     // win.  The lane-per-rank kernel runs only when its tunable asks for it.
-    if (dest_groups <= 1 && P >= tuning().lpr_min_ranks) {
+    // 9 to 15 ranks take the tile kernel too, unless the tunable says from where
+    // (12 ranks of bf16: 2.30 against 3.29 us at 64 KiB per rank, 3.49 against
+    // 4.19 at 256 KiB; up to 8 ranks the direct kernel is faster).
+    const int many = tuning().lpr_min_ranks;
+    if (dest_groups <= 1 && (P >= many || (many == kManyRanks && P > 8))) {
         if (static_cast<int64_t>(bytes / 16) * P <= tuning().lpr_max_vectors)
             return launch_allreduce_lpr(in, out, P, count, dtype, mode, stream);
         int tv = tuning().tile_v;

@@ -69,10 +69,14 @@ __global__ __launch_bounds__(kWG) void k_reduce_scatter(Ptrs<MAXP> p, RsShape s,
 
 // Direct reduce-scatter: grid (chunks per shard, P), workgroup (c, r) reduces
 // chunk c of shard r; everything it reads from its arguments sits at fixed
-// offsets (see k_allreduce_direct).
+// offsets (see k_allreduce_direct; rank counts other than 2, 4, 8 and 16 as
+// there).
 template <int PT, int DT, int VPT, bool KEEP>
-__global__ __launch_bounds__(kWG) void k_reduce_scatter_direct(Ptrs<PT> p, int64_t mv) {
-    pin_args(p, mv, blockDim.x, blockIdx.y);
+__global__ __launch_bounds__(kWG) void k_reduce_scatter_direct(Ptrs<rank_cap<PT>()> p, int64_t mv, int32_t ranks) {
+    if constexpr (PT > 0)
+        pin_args(p, mv, blockDim.x, blockIdx.y);
+    else
+        pin_args(p, mv, blockDim.x, blockIdx.y, ranks);
     const int nt = blockDim.x;
     const int64_t cv = static_cast<int64_t>(nt) * VPT;
     const int64_t c = blockIdx.x;
@@ -80,12 +84,13 @@ __global__ __launch_bounds__(kWG) void k_reduce_scatter_direct(Ptrs<PT> p, int64
     const int64_t v0 = c * cv + threadIdx.x;
     RsShape s{};
     s.mv = mv;
-    s.P = PT;
-    const RankTable tab{0u, 0u, 0u, 0u};  // compile-time rank count: pointers come from the arguments
+    const RankTable tab{0u, 0u, 0u, 0u};  // pointers come from the arguments
+    constexpr int N = rank_cap<PT>();
+    const int P = PT > 0 ? PT : ranks;
     if ((c + 1) * cv <= mv)
-        reduce_scatter_chunk<PT, DT, VPT, true, KEEP, PT, (PT <= 8)>(p, tab, s, PT, r, v0, nt);
+        reduce_scatter_chunk<PT, DT, VPT, true, KEEP, N, (N <= 8)>(p, tab, s, P, r, v0, nt);
     else
-        reduce_scatter_chunk<PT, DT, VPT, false, KEEP, PT, (PT <= 8)>(p, tab, s, PT, r, v0, nt);
+        reduce_scatter_chunk<PT, DT, VPT, false, KEEP, N, (N <= 8)>(p, tab, s, P, r, v0, nt);
 }
 
 // Element-wise fallback when a shard is not a whole number of 16-byte vectors.
@@ -173,8 +178,12 @@ __global__ __launch_bounds__(kWG) void k_all_gather(Ptrs<MAXP> p, AgShape s, Pla
 // The source pointer is an argument indexed by the workgroup's y index; the
 // destinations are compile-time offsets (see k_allreduce_direct).
 template <int PT, int VPT, bool CACHED, bool WT>
-__global__ __launch_bounds__(kWG) void k_all_gather_direct(Ptrs<PT> p, int64_t mv, int32_t gap) {
-    pin_args(p, mv, gap, blockDim.x);
+__global__ __launch_bounds__(kWG) void k_all_gather_direct(Ptrs<rank_cap<PT>()> p, int64_t mv, int32_t gap,
+                                                           int32_t ranks) {
+    if constexpr (PT > 0)
+        pin_args(p, mv, gap, blockDim.x);
+    else
+        pin_args(p, mv, gap, blockDim.x, ranks);
     const int nt = blockDim.x;
     const int64_t cv = static_cast<int64_t>(nt) * VPT;
     const int64_t c = blockIdx.x;
@@ -188,20 +197,21 @@ __global__ __launch_bounds__(kWG) void k_all_gather_direct(Ptrs<PT> p, int64_t m
     else
         load_vecs<false, VPT, !CACHED>(y, src, v0, nt, mv);
 #pragma unroll
-    for (int d = 0; d < PT; ++d) {
+    for (int d = 0; d < rank_cap<PT>(); ++d) {
         uint4* dst = p.out[d] + r * mv;
-        if (dst == src) continue;  // in-place shard
-        if (d > 0) store_gap(gap);
-        if constexpr (WT) {
-            if (full)
-                store_vecs_wt<true, VPT>(dst + c * cv, y, static_cast<int>(threadIdx.x), nt, mv - c * cv);
-            else
-                store_vecs_wt<false, VPT>(dst + c * cv, y, static_cast<int>(threadIdx.x), nt, mv - c * cv);
-        } else {
-            if (full)
-                store_vecs<true, VPT>(dst, y, v0, nt, mv);
-            else
-                store_vecs<false, VPT>(dst, y, v0, nt, mv);
+        if ((PT > 0 || d < ranks) && dst != src) {  // dst == src: in-place shard
+            if (d > 0) store_gap(gap);
+            if constexpr (WT) {
+                if (full)
+                    store_vecs_wt<true, VPT>(dst + c * cv, y, static_cast<int>(threadIdx.x), nt, mv - c * cv);
+                else
+                    store_vecs_wt<false, VPT>(dst + c * cv, y, static_cast<int>(threadIdx.x), nt, mv - c * cv);
+            } else {
+                if (full)
+                    store_vecs<true, VPT>(dst, y, v0, nt, mv);
+                else
+                    store_vecs<false, VPT>(dst, y, v0, nt, mv);
+            }
         }
     }
 }
@@ -227,8 +237,8 @@ template <int PT, int MAXP, int DT, int VPT, bool KEEP>
 void launch_rs_t(const void* const* in, void* const* out, int P, const RsShape& s, const Place& pl, int64_t G, int nt,
                  hipStream_t st) {
     Ptrs<MAXP> p = make_ptrs<MAXP>(in, out, P, P);
-    hipLaunchKernelGGL((k_reduce_scatter<PT, MAXP, DT, VPT, KEEP>), dim3(static_cast<unsigned>(G)), dim3(nt), 0, st, p,
-                       s, pl);
+    hipLaunchKernelGGL((k_reduce_scatter<PT, MAXP, DT, VPT, KEEP>), dim3(static_cast<unsigned>(G)), dim3(nt), 0, st, p, s,
+                       pl);
 }
 
 template <int DT, int VPT, bool KEEP>
@@ -251,44 +261,48 @@ void launch_rs_p(const void* const* in, void* const* out, int P, const RsShape& 
     }
 }
 
-}  // namespace
-
 template <int PT, int DT, int VPT, bool KEEP>
 void launch_rs_direct_t(const void* const* in, void* const* out, const RsShape& s, int nt, hipStream_t st) {
-    const Ptrs<PT> p = make_ptrs<PT>(in, out, PT, PT);
+    const auto p = make_ptrs<rank_cap<PT>()>(in, out, s.P, s.P);
     hipLaunchKernelGGL((k_reduce_scatter_direct<PT, DT, VPT, KEEP>),
-                       dim3(static_cast<unsigned>(s.wcs), static_cast<unsigned>(PT)), dim3(nt), 0, st, p, s.mv);
+                       dim3(static_cast<unsigned>(s.wcs), static_cast<unsigned>(s.P)), dim3(nt), 0, st, p, s.mv, s.P);
 }
 
 template <int DT, int VPT, bool KEEP>
-void launch_rs_direct_p(const void* const* in, void* const* out, int P, const RsShape& s, int nt, hipStream_t st) {
-    switch (P) {
+void launch_rs_direct_p(const void* const* in, void* const* out, const RsShape& s, int nt, hipStream_t st) {
+    switch (s.P) {
         case 2: launch_rs_direct_t<2, DT, VPT, KEEP>(in, out, s, nt, st); break;
         case 4: launch_rs_direct_t<4, DT, VPT, KEEP>(in, out, s, nt, st); break;
         case 8: launch_rs_direct_t<8, DT, VPT, KEEP>(in, out, s, nt, st); break;
-        default: launch_rs_direct_t<16, DT, VPT, KEEP>(in, out, s, nt, st); break;
+        case 16: launch_rs_direct_t<16, DT, VPT, KEEP>(in, out, s, nt, st); break;
+        default:
+            if (s.P < 4) launch_rs_direct_t<-4, DT, VPT, KEEP>(in, out, s, nt, st);
+            else if (s.P < 8) launch_rs_direct_t<-8, DT, VPT, KEEP>(in, out, s, nt, st);
+            else launch_rs_direct_t<-16, DT, VPT, KEEP>(in, out, s, nt, st);
+            break;
     }
 }
 
-// Every uncapped reduce-scatter of 2, 4, 8 or 16 ranks (single-item groups,
-// so both placements run the linear map).
-hipError_t launch_rs_direct(const void* const* in, void* const* out, int P, const RsShape& s, int dtype, int vpt,
-                            int nt, bool keep, hipStream_t st) {
-    if (dtype == kDtF32) {
-        if (keep) launch_rs_direct_p<kDtF32, 1, true>(in, out, P, s, nt, st);
-        else launch_rs_direct_p<kDtF32, 1, false>(in, out, P, s, nt, st);
-    } else if (vpt == 4) {
-        if (keep) launch_rs_direct_p<kDtBf16, 4, true>(in, out, P, s, nt, st);
-        else launch_rs_direct_p<kDtBf16, 4, false>(in, out, P, s, nt, st);
-    } else if (vpt == 2) {
-        if (keep) launch_rs_direct_p<kDtBf16, 2, true>(in, out, P, s, nt, st);
-        else launch_rs_direct_p<kDtBf16, 2, false>(in, out, P, s, nt, st);
-    } else {
-        if (keep) launch_rs_direct_p<kDtBf16, 1, true>(in, out, P, s, nt, st);
-        else launch_rs_direct_p<kDtBf16, 1, false>(in, out, P, s, nt, st);
-    }
-    return hipGetLastError();
+// Launch by dtype and vectors per thread.
+template <bool KEEP>
+void launch_rs(bool direct, const void* const* in, void* const* out, const RsShape& s, int dtype, int vpt,
+               const Place& pl, int64_t G, int nt, hipStream_t st) {
+    auto go = [&](auto dt, auto v) {
+        if (direct)
+            launch_rs_direct_p<dt(), v(), KEEP>(in, out, s, nt, st);
+        else
+            launch_rs_p<dt(), v(), KEEP>(in, out, s.P, s, pl, G, nt, st);
+    };
+    using F32 = std::integral_constant<int, kDtF32>;
+    using Bf16 = std::integral_constant<int, kDtBf16>;
+    using V1 = std::integral_constant<int, 1>;
+    using V2 = std::integral_constant<int, 2>;
+    using V4 = std::integral_constant<int, 4>;
+    if (dtype == kDtF32) vpt == 4 ? go(F32{}, V4{}) : vpt == 2 ? go(F32{}, V2{}) : go(F32{}, V1{});
+    else vpt == 4 ? go(Bf16{}, V4{}) : vpt == 2 ? go(Bf16{}, V2{}) : go(Bf16{}, V1{});
 }
+
+}  // namespace
 
 hipError_t launch_reduce_scatter(const void* const* in, void* const* out, int P, size_t m, int dtype, int mode,
                                  bool keep_output, hipStream_t stream) {
@@ -317,24 +331,10 @@ hipError_t launch_reduce_scatter(const void* const* in, void* const* out, int P,
     const Place pl = make_place_uniform(mode, s.wcs * P, 1);
     const int64_t G = cap_grid(place_grid(pl));
     // Every work item is its own group: both placements run the linear map.
-    if (G == s.wcs * P && G <= direct_max_grid() && (P == 2 || P == 4 || P == 8 || P == 16)) {
-        note_launch("k_reduce_scatter_direct", kMapLinear, 1, G, nt, vpt);
-        return launch_rs_direct(in, out, P, s, dtype, vpt, nt, keep_output, stream);
-    }
-    note_launch("k_reduce_scatter", kMapLinear, 1, G, nt, vpt);
-    if (dtype == kDtF32) {
-        if (keep_output) launch_rs_p<kDtF32, 1, true>(in, out, P, s, pl, G, nt, stream);
-        else launch_rs_p<kDtF32, 1, false>(in, out, P, s, pl, G, nt, stream);
-    } else if (vpt == 4) {
-        if (keep_output) launch_rs_p<kDtBf16, 4, true>(in, out, P, s, pl, G, nt, stream);
-        else launch_rs_p<kDtBf16, 4, false>(in, out, P, s, pl, G, nt, stream);
-    } else if (vpt == 2) {
-        if (keep_output) launch_rs_p<kDtBf16, 2, true>(in, out, P, s, pl, G, nt, stream);
-        else launch_rs_p<kDtBf16, 2, false>(in, out, P, s, pl, G, nt, stream);
-    } else {
-        if (keep_output) launch_rs_p<kDtBf16, 1, true>(in, out, P, s, pl, G, nt, stream);
-        else launch_rs_p<kDtBf16, 1, false>(in, out, P, s, pl, G, nt, stream);
-    }
+    const bool direct = G == s.wcs * P && G <= direct_max_grid() && P <= 16;
+    note_launch(direct ? "k_reduce_scatter_direct" : "k_reduce_scatter", kMapLinear, 1, G, nt, vpt);
+    if (keep_output) launch_rs<true>(direct, in, out, s, dtype, vpt, pl, G, nt, stream);
+    else launch_rs<false>(direct, in, out, s, dtype, vpt, pl, G, nt, stream);
     return hipGetLastError();
 }
 
@@ -342,19 +342,19 @@ hipError_t launch_reduce_scatter(const void* const* in, void* const* out, int P,
 template <int PT>
 void launch_ag_direct_p(const void* const* in, void* const* out, const AgShape& s, int vpt, bool cached, bool wt,
                         dim3 g, dim3 b, hipStream_t st) {
-    const Ptrs<PT> p = make_ptrs<PT>(in, out, PT, PT);
+    const auto p = make_ptrs<rank_cap<PT>()>(in, out, s.P, s.P);
     if (cached && wt && PT == 8) {
-        if (vpt == 4) hipLaunchKernelGGL((k_all_gather_direct<PT, 4, true, true>), g, b, 0, st, p, s.mv, s.gap);
-        else if (vpt == 2) hipLaunchKernelGGL((k_all_gather_direct<PT, 2, true, true>), g, b, 0, st, p, s.mv, s.gap);
-        else hipLaunchKernelGGL((k_all_gather_direct<PT, 1, true, true>), g, b, 0, st, p, s.mv, s.gap);
+        if (vpt == 4) hipLaunchKernelGGL((k_all_gather_direct<PT, 4, true, true>), g, b, 0, st, p, s.mv, s.gap, s.P);
+        else if (vpt == 2) hipLaunchKernelGGL((k_all_gather_direct<PT, 2, true, true>), g, b, 0, st, p, s.mv, s.gap, s.P);
+        else hipLaunchKernelGGL((k_all_gather_direct<PT, 1, true, true>), g, b, 0, st, p, s.mv, s.gap, s.P);
     } else if (cached) {
-        if (vpt == 4) hipLaunchKernelGGL((k_all_gather_direct<PT, 4, true, false>), g, b, 0, st, p, s.mv, s.gap);
-        else if (vpt == 2) hipLaunchKernelGGL((k_all_gather_direct<PT, 2, true, false>), g, b, 0, st, p, s.mv, s.gap);
-        else hipLaunchKernelGGL((k_all_gather_direct<PT, 1, true, false>), g, b, 0, st, p, s.mv, s.gap);
+        if (vpt == 4) hipLaunchKernelGGL((k_all_gather_direct<PT, 4, true, false>), g, b, 0, st, p, s.mv, s.gap, s.P);
+        else if (vpt == 2) hipLaunchKernelGGL((k_all_gather_direct<PT, 2, true, false>), g, b, 0, st, p, s.mv, s.gap, s.P);
+        else hipLaunchKernelGGL((k_all_gather_direct<PT, 1, true, false>), g, b, 0, st, p, s.mv, s.gap, s.P);
     } else {
-        if (vpt == 4) hipLaunchKernelGGL((k_all_gather_direct<PT, 4, false, false>), g, b, 0, st, p, s.mv, s.gap);
-        else if (vpt == 2) hipLaunchKernelGGL((k_all_gather_direct<PT, 2, false, false>), g, b, 0, st, p, s.mv, s.gap);
-        else hipLaunchKernelGGL((k_all_gather_direct<PT, 1, false, false>), g, b, 0, st, p, s.mv, s.gap);
+        if (vpt == 4) hipLaunchKernelGGL((k_all_gather_direct<PT, 4, false, false>), g, b, 0, st, p, s.mv, s.gap, s.P);
+        else if (vpt == 2) hipLaunchKernelGGL((k_all_gather_direct<PT, 2, false, false>), g, b, 0, st, p, s.mv, s.gap, s.P);
+        else hipLaunchKernelGGL((k_all_gather_direct<PT, 1, false, false>), g, b, 0, st, p, s.mv, s.gap, s.P);
     }
 }
 
@@ -413,16 +413,26 @@ hipError_t launch_all_gather(const void* const* in, void* const* out, int P, siz
     // ranks it takes grids beyond the direct-grid limit too: against the general
     // kernel's persistent loop it measured 6-10 % faster at 6-32 MiB shards on
     // MI355X (103 against 114 us at 8 MiB, 418 against 457 us at 32 MiB).
+    // With 9 to 16 ranks only from 3 MiB per output: the 16-slot kernel loads its
+    // pointers where it uses them, and below that the general kernel's rank
+    // table is faster (16 ranks, 16 KiB shards 3.15 against 4.25 us; 12 ranks,
+    // 512 KiB shards 14.2 against 13.4).
     const int64_t items = s.wcs * P;
     const bool direct = gsize == 1 && (P == 8 ? items <= grid_limit(kAgDirectMaxGrid8)
-                                              : (P == 2 || P == 4) && G == items && G <= direct_max_grid());
+                                              : P <= 16 && G == items && G <= direct_max_grid() &&
+                                                    (P < 8 || s.mv * P >= (int64_t(3) << 16)));
     if (direct) {
         note_launch("k_all_gather_direct", kMapLinear, 1, items, nt, vpt);
         const dim3 g(static_cast<unsigned>(s.wcs), static_cast<unsigned>(P)), b(nt);
         switch (P) {
             case 2: launch_ag_direct_p<2>(in, out, s, vpt, src_cached, false, g, b, stream); break;
             case 4: launch_ag_direct_p<4>(in, out, s, vpt, src_cached, false, g, b, stream); break;
-            default: launch_ag_direct_p<8>(in, out, s, vpt, src_cached, wt, g, b, stream); break;
+            case 8: launch_ag_direct_p<8>(in, out, s, vpt, src_cached, wt, g, b, stream); break;
+            default:
+                if (P < 4) launch_ag_direct_p<-4>(in, out, s, vpt, src_cached, false, g, b, stream);
+                else if (P < 8) launch_ag_direct_p<-8>(in, out, s, vpt, src_cached, false, g, b, stream);
+                else launch_ag_direct_p<-16>(in, out, s, vpt, src_cached, false, g, b, stream);
+                break;
         }
         return hipGetLastError();
     }

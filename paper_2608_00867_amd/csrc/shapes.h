@@ -12,7 +12,8 @@
 namespace nuna {
 namespace {
 
-inline bool direct_ranks(int P, int vpt) { return P == 2 || P == 4 || P == 8 || (P == 16 && vpt != 8); }
+// The direct kernels exist for up to 16 ranks; 8 vectors per thread for 2, 4 and 8.
+inline bool direct_ranks(int P, int vpt) { return P == 2 || P == 4 || P == 8 || (P <= 16 && vpt != 8); }
 
 // Largest grid that takes the direct kernels (NUNA_DIRECT_MAX_GRID, default
 // 8192).  Beyond it the general kernels run: at 64 MiB per rank with one
@@ -122,22 +123,56 @@ inline int pick_threads(int64_t vectors_per_rank, int P) {
     return kWG;
 }
 
-// Reduce-scatter launch shape by the vectors each input rank holds (P
-// shards), for up to 16 ranks (measured on MI355X with bf16, 8 ranks, cold):
-// 4 vectors per thread from 8 MiB per input rank, where it was 7-9 % faster
-// than the all-reduce's shapes; 128 threads with 2 at 4 MiB; the
-// all-reduce's rule below that.  Forced tunables win.
+// Launch shapes by size: rows in quarter MiB (per rank, as the rule using them
+// says), each row holding from its size on; nt 0 leaves the shape as it was.
+struct ShapeRow {
+    int32_t from;
+    int32_t nt, vpt;
+};
+
+template <int N>
+void row_shape(const ShapeRow (&rows)[N], int64_t vectors, int& nt, int& vpt) {
+    constexpr int64_t kQuarter = int64_t(1) << 14;  // vectors in a quarter MiB
+    const ShapeRow* hit = nullptr;
+    for (const ShapeRow& r : rows)
+        if (r.from * kQuarter <= vectors) hit = &r;
+    if (hit && hit->nt > 0) {
+        nt = hit->nt;
+        vpt = hit->vpt;
+    }
+}
+
+// Reduce-scatter launch shape by the input bytes per rank (P shards), for up
+// to 16 ranks, both dtypes.  Small calls want many one-wave workgroups, from
+// about 4 MiB the rounds of resident workgroups decide (see the one-shot's
+// rows), from 8 MiB long contiguous chunks.  us per call in graphs on MI355X
+// (3 buffer sets in turn), the shared rule (fp32: 1 vector per thread) against
+// the row taken:
+//   8 ranks   512 KiB f32 2.36 -> 2.15 (64x1), 1.5 MiB 3.66 -> 3.27 (64x1), 4 MiB 7.6 -> 6.6 (64x4),
+//             8 MiB f32 15.7 -> 12.8 (256x4), 32 MiB f32 57.0 -> 53.8 (256x4)
+//   4 ranks   1 MiB 2.21 -> 1.96 (64x1), 8 MiB f32 8.8 -> 7.2 (64x4), 11 MiB f32 11.8 -> 10.4 (256x4)
+//   12 ranks  512 KiB 3.5 -> 3.1 (64x1), 16 MiB bf16 46.9 -> 41.2 (256x2)
+//   16 ranks  2 MiB 7.4 -> 6.6 (256x2), 4 MiB f32 15.0 -> 12.1 (256x4), 8 MiB f32 27.2 -> 25.7 (256x4)
+// Forced tunables win.
 inline void pick_rs_shape(int64_t in_vectors, int P, int dtype, int& nt, int& vpt) {
     nt = pick_threads(in_vectors, P);
-    vpt = dtype == kDtBf16 ? pick_vpt(in_vectors, P) : 1;
-    if (P > 16 || dtype != kDtBf16 || tuning().wg_threads || tuning().vpt) return;
-    if (in_vectors >= (int64_t(1) << 19)) {
-        nt = 256;
-        vpt = 4;
-    } else if (in_vectors >= (int64_t(1) << 18)) {
-        nt = 128;
-        vpt = 2;
-    }
+    vpt = dtype == kDtBf16 || tuning().vpt ? pick_vpt(in_vectors, P) : 1;
+    if (P > 16 || tuning().wg_threads || tuning().vpt) return;
+    if (P <= 2 && dtype == kDtF32) return;  // 256x4 lost 3-10 % from 5 MiB
+    static constexpr ShapeRow k3[] = {{16, 128, 2}, {32, 256, 4}};
+    static constexpr ShapeRow k4[] = {{3, 64, 1}, {7, 0, 0}, {16, 64, 4}, {32, 256, 4}};
+    static constexpr ShapeRow k7[] = {{2, 64, 1}, {15, 128, 2}, {32, 256, 4}};
+    static constexpr ShapeRow k8[] = {{1, 64, 1}, {7, 0, 0}, {16, 64, 4}, {32, 256, 4}};
+    static constexpr ShapeRow k15[] = {{1, 64, 1}, {7, 0, 0}, {16, 128, 2}, {18, 256, 2}, {30, 128, 2},
+                                       {40, 256, 2}};
+    static constexpr ShapeRow k16[] = {{2, 128, 1}, {3, 0, 0}, {5, 256, 2}, {10, 128, 2}, {14, 256, 4}, {18, 256, 2},
+                                       {28, 256, 4}};
+    if (P <= 3) row_shape(k3, in_vectors, nt, vpt);
+    else if (P == 4) row_shape(k4, in_vectors, nt, vpt);
+    else if (P <= 7) row_shape(k7, in_vectors, nt, vpt);
+    else if (P == 8) row_shape(k8, in_vectors, nt, vpt);
+    else if (P <= 15) row_shape(k15, in_vectors, nt, vpt);
+    else row_shape(k16, in_vectors, nt, vpt);
 }
 
 // All-gather launch shape by the vectors each output rank receives, for up
@@ -145,8 +180,10 @@ inline void pick_rs_shape(int64_t in_vectors, int P, int dtype, int& nt, int& vp
 // workgroups with 1 vector per thread below 2 MiB per output, 64 threads with
 // 4 vectors below 16 MiB, 5-20 % faster than the all-reduce's shapes.  From
 // 16 MiB per output, 8 ranks have a rule of their own (below); other rank
-// counts take 128 threads with 4 vectors below 64 MiB and 128 with 1 beyond.
-// Forced tunables win.
+// counts take 128 threads with 4 vectors below 20 MiB and 256 with 2 beyond,
+// with up to 7 ranks 256 with 1 from 56 MiB (against 128 x 4 below 64 MiB and
+// 128 x 1 beyond: 4 ranks 23 MiB 23.3 -> 21.4 us, 6 ranks 45 MiB 65.4 -> 62.9 and
+// 64 MiB 92.3 -> 83.9, 12 ranks 32 MiB 88.2 -> 83.2).  Forced tunables win.
 inline void pick_ag_shape(int64_t out_vectors, int P, int& nt, int& vpt) {
     nt = pick_threads(out_vectors, P);
     vpt = pick_vpt(out_vectors, P);
@@ -164,12 +201,12 @@ inline void pick_ag_shape(int64_t out_vectors, int P, int& nt, int& vpt) {
         // 42.8 us at 3 MiB), best or within 1 % of the best shape at 4-32 MiB.
         nt = 256;
         vpt = 1;
-    } else if (out_vectors < (int64_t(1) << 22)) {
+    } else if (out_vectors < (int64_t(5) << 18)) {
         nt = 128;
         vpt = 4;
     } else {
-        nt = 128;
-        vpt = 1;
+        nt = 256;
+        vpt = P > 8 || out_vectors < (int64_t(7) << 19) ? 2 : 1;
     }
 }
 
@@ -193,23 +230,11 @@ inline void pick_ag_shape(int64_t out_vectors, int P, int& nt, int& vpt) {
 // Each row begins where it stopped losing (2 ranks of f32 at 3.25 MiB: 64x8
 // 3.4 against 2.9 us; 4 ranks of bf16 at 3.25-3.75 MiB: 256x2 5.1-5.6 us, 64x8
 // 5.6-6.1, the shared 256x1 5.9-6.6).
-struct ShapeRow {
-    int32_t from;  // quarter MiB per rank from which the row holds
-    int32_t nt, vpt;  // 0: the shared rule
-};
-
-template <int N>
-void ar_row_shape(const ShapeRow (&rows)[N], int64_t vectors_per_rank, int& nt, int& vpt) {
-    constexpr int64_t kQuarter = int64_t(1) << 14;  // vectors in a quarter MiB
-    const ShapeRow* hit = nullptr;
-    for (const ShapeRow& r : rows)
-        if (r.from * kQuarter <= vectors_per_rank) hit = &r;
-    if (hit && hit->nt > 0) {
-        nt = hit->nt;
-        vpt = hit->vpt;
-    }
-}
-
+// Rank counts without rows of their own in this list run the kernels with a
+// run-time count:
+//   3 ranks        3 MiB 4.33 -> 3.92 (64x4)
+//   5-7 ranks      1.5 MiB 4.1-5.0 -> 3.6-4.7 (64x1), 8 MiB 15.4-22.9 -> 15.0-21.2 (256x4)
+//   9-15 ranks     3 MiB 14.3 -> 12.9 (128x2), 6 MiB 30.8 -> 27.2 (128x2)
 // 8 ranks, 8-32 MiB per rank: 8 vectors per thread in 256-thread workgroups.
 // That kernel holds 256 VGPRs, so one workgroup per CU runs at a time and
 // the launch proceeds in rounds of 256 workgroups, each moving 32 KiB
@@ -238,15 +263,17 @@ inline void pick_ar_shape(int64_t vectors_per_rank, int P, int dtype, int& nt, i
                                         {64, 0, 0}};
     static constexpr ShapeRow k16b[] = {{5, 256, 2}, {9, 64, 2}, {13, 64, 4}, {15, 0, 0}, {20, 128, 2}, {26, 0, 0},
                                         {34, 128, 2}, {64, 0, 0}};
-    switch (P) {
-        case 2: f32 ? ar_row_shape(k2f, vectors_per_rank, nt, vpt) : ar_row_shape(k2b, vectors_per_rank, nt, vpt); break;
-        case 4: f32 ? ar_row_shape(k4f, vectors_per_rank, nt, vpt) : ar_row_shape(k4b, vectors_per_rank, nt, vpt); break;
-        case 8: f32 ? ar_row_shape(k8f, vectors_per_rank, nt, vpt) : ar_row_shape(k8b, vectors_per_rank, nt, vpt); break;
-        case 16:
-            f32 ? ar_row_shape(k16f, vectors_per_rank, nt, vpt) : ar_row_shape(k16b, vectors_per_rank, nt, vpt);
-            break;
-        default: break;
-    }
+    static constexpr ShapeRow k3[] = {{10, 64, 4}, {14, 0, 0}};
+    static constexpr ShapeRow k7[] = {{5, 64, 1}, {7, 0, 0}, {28, 256, 4}, {56, 0, 0}};
+    static constexpr ShapeRow k15[] = {{10, 128, 2}, {14, 0, 0}, {18, 128, 2}, {30, 256, 4}, {38, 128, 2}, {56, 0, 0}};
+    const int64_t v = vectors_per_rank;
+    if (P == 2) f32 ? row_shape(k2f, v, nt, vpt) : row_shape(k2b, v, nt, vpt);
+    else if (P == 3) row_shape(k3, v, nt, vpt);
+    else if (P == 4) f32 ? row_shape(k4f, v, nt, vpt) : row_shape(k4b, v, nt, vpt);
+    else if (P >= 5 && P <= 7) row_shape(k7, v, nt, vpt);
+    else if (P == 8) f32 ? row_shape(k8f, v, nt, vpt) : row_shape(k8b, v, nt, vpt);
+    else if (P >= 9 && P <= 15) row_shape(k15, v, nt, vpt);
+    else if (P == 16) f32 ? row_shape(k16f, v, nt, vpt) : row_shape(k16b, v, nt, vpt);
     if (P != 8 || vectors_per_rank <= (int64_t(1) << 19) || vectors_per_rank > (int64_t(1) << 21)) return;
     constexpr int64_t kChunk = 256 * 8, kRound = 256;
     const int64_t G = (vectors_per_rank + kChunk - 1) / kChunk;

@@ -90,3 +90,58 @@ def test_allreduce_shape_edges(nuna, P, dtype, quarter):
         got = _run(lambda i, o: nuna.allreduce(i, o, algo="one_shot"), x, n, what)
         for d in (0, P // 2, P - 1):
             assert_bitwise(got[d], ref[d], f"{what} rank {d}")
+
+
+# ---------------------------------------------------------------- rank counts without a kernel of their own
+
+@pytest.mark.parametrize("P", [1, 3, 5, 6, 7, 9, 12, 15])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_run_time_rank_counts(nuna, P, dtype):
+    """All-reduce, reduce-scatter and all-gather of every register bucket of run-time rank counts (up to 4,
+    8 and 16), one vector, a chunk and a vector, and sizes of the shape rows; in place too."""
+    es = 2 if dtype == "bf16" else 4
+    lanes = 16 // es
+    for n in (lanes, 1024 * lanes + lanes + 1, 5 * (1 << 16) * lanes + 3, 7 * (1 << 17) * lanes):
+        what = f"P={P} {dtype} n={n}"
+        x = _values(P, n, dtype, 31 * P + n % 97)
+        ref = oracle.allreduce(x)
+        got = _run(nuna.allreduce, x, n, what)
+        bufs = [to_dev(a) for a in x]
+        nuna.allreduce(bufs, bufs, algo="one_shot")
+        torch.cuda.synchronize()
+        for d in {0, P // 2, P - 1}:
+            assert_bitwise(got[d], ref[d], f"{what} rank {d}")
+            assert_bitwise(to_host(bufs[d]), ref[d], f"{what} in place rank {d}")
+    for m in (lanes, 129 * lanes, ((1 << 17) // P + 5) * lanes, ((5 << 18) // P + 1) * lanes):
+        what = f"P={P} {dtype} m={m}"
+        x = _values(P, P * m, dtype, 37 * P + m % 89)
+        ref = oracle.reduce_scatter(x)
+        got = _run(nuna.reduce_scatter, x, m, "RS " + what)
+        src = [a[:m].copy() for a in x]
+        ref_g = oracle.all_gather(src)
+        got_g = _run(nuna.all_gather, src, P * m, "AG " + what)
+        bufs = [torch.zeros(P * m, dtype=to_dev(src[0]).dtype, device="cuda") for _ in range(P)]
+        for r in range(P):
+            bufs[r][r * m:(r + 1) * m].copy_(to_dev(src[r]))
+        nuna.all_gather([bufs[r][r * m:(r + 1) * m] for r in range(P)], bufs)
+        torch.cuda.synchronize()
+        for d in {0, P // 2, P - 1}:
+            assert_bitwise(got[d], ref[d], f"RS {what} rank {d}")
+            assert_bitwise(got_g[d], ref_g[d], f"AG {what} rank {d}")
+            assert_bitwise(to_host(bufs[d]), ref_g[d], f"AG {what} in place rank {d}")
+
+
+RS_EDGES = [(2, 32), (4, 3), (4, 16), (4, 32), (8, 1), (8, 7), (8, 16), (8, 32), (12, 18), (12, 30), (16, 2), (16, 5),
+            (16, 10), (16, 14), (16, 18), (16, 28)]
+
+
+@pytest.mark.parametrize("P,quarter", RS_EDGES)
+def test_reduce_scatter_shape_edges(nuna, P, quarter):
+    """fp32, shards one vector below and above each size where the launch shape changes."""
+    at = quarter * (1 << 14) // P  # vectors per shard
+    for mv in (at - 1, at + 1):
+        x = wl.normal_f32(P, P * mv * 4, 41 * quarter + P)
+        ref = oracle.reduce_scatter(x)
+        got = _run(nuna.reduce_scatter, x, mv * 4, f"P={P} mv={mv}")
+        for r in (0, P - 1):
+            assert_bitwise(got[r], ref[r], f"P={P} mv={mv} rank {r}")
