@@ -65,9 +65,8 @@ struct Arith<kDtF32> {
         return make_uint4(__float_as_uint(a[0]), __float_as_uint(a[1]), __float_as_uint(a[2]),
                           __float_as_uint(a[3]));
     }
-    __device__ static __forceinline__ float load1(const void* p, int64_t i) {
-        return static_cast<const float*>(p)[i];
-    }
+    using Raw = float;
+    __device__ static __forceinline__ float widen1(float v) { return v; }
     __device__ static __forceinline__ void store1(void* p, int64_t i, float v) { static_cast<float*>(p)[i] = v; }
 };
 
@@ -99,9 +98,8 @@ struct Arith<kDtBf16> {
         return make_uint4(f32_to_bf16x2(a[0], a[1]), f32_to_bf16x2(a[2], a[3]), f32_to_bf16x2(a[4], a[5]),
                           f32_to_bf16x2(a[6], a[7]));
     }
-    __device__ static __forceinline__ float load1(const void* p, int64_t i) {
-        return bf16_lo(static_cast<const uint16_t*>(p)[i]);
-    }
+    using Raw = uint16_t;
+    __device__ static __forceinline__ float widen1(uint16_t v) { return bf16_lo(v); }
     __device__ static __forceinline__ void store1(void* p, int64_t i, float v) {
         static_cast<uint16_t*>(p)[i] = static_cast<uint16_t>(f32_to_bf16x2(v, 0.0f));
     }
@@ -130,6 +128,20 @@ __device__ __forceinline__ uint4 load16(const uint4* p) {
     } else {
         return *p;
     }
+}
+
+// 16 bytes from an address that is aligned to its elements only: one
+// global_load_dwordx4 (global memory takes any alignment on this hardware).
+typedef unsigned int u32x4_any_t __attribute__((ext_vector_type(4), aligned(2)));
+
+template <bool NT>
+__device__ __forceinline__ uint4 load16_any(const char* p) {
+    u32x4_any_t t;
+    if constexpr (NT)
+        t = __builtin_nontemporal_load(reinterpret_cast<const u32x4_any_t*>(p));
+    else
+        t = *reinterpret_cast<const u32x4_any_t*>(p);
+    return make_uint4(t.x, t.y, t.z, t.w);
 }
 
 // ---------------------------------------------------------------- kernel arguments
@@ -173,6 +185,26 @@ constexpr int rank_cap() {
 #define NUNA_PIN_PTRS4(p) \
     "s"(p.in[0]), "s"(p.in[1]), "s"(p.in[2]), "s"(p.in[3]), "s"(p.out[0]), "s"(p.out[1]), "s"(p.out[2]), "s"(p.out[3])
 #define NUNA_PIN_PTRS2(p) "s"(p.in[0]), "s"(p.in[1]), "s"(p.out[0]), "s"(p.out[1])
+
+// Sixteen slots: the input pointers in one statement, the output pointers in
+// another (a statement takes 30 operands).  In the kernels with a run-time rank
+// count each pointer would otherwise be loaded and waited for inside its own
+// rank's test, sixteen round trips.
+template <int N>
+__device__ __forceinline__ void pin_inputs16(const Ptrs<N>& p) {
+    static_assert(N == 16, "sixteen slots");
+    asm volatile("" ::"s"(p.in[0]), "s"(p.in[1]), "s"(p.in[2]), "s"(p.in[3]), "s"(p.in[4]), "s"(p.in[5]), "s"(p.in[6]),
+                 "s"(p.in[7]), "s"(p.in[8]), "s"(p.in[9]), "s"(p.in[10]), "s"(p.in[11]), "s"(p.in[12]), "s"(p.in[13]),
+                 "s"(p.in[14]), "s"(p.in[15]));
+}
+
+template <int N>
+__device__ __forceinline__ void pin_outputs16(const Ptrs<N>& p) {
+    static_assert(N == 16, "sixteen slots");
+    asm volatile("" ::"s"(p.out[0]), "s"(p.out[1]), "s"(p.out[2]), "s"(p.out[3]), "s"(p.out[4]), "s"(p.out[5]),
+                 "s"(p.out[6]), "s"(p.out[7]), "s"(p.out[8]), "s"(p.out[9]), "s"(p.out[10]), "s"(p.out[11]),
+                 "s"(p.out[12]), "s"(p.out[13]), "s"(p.out[14]), "s"(p.out[15]));
+}
 
 template <int N, class A, class B, class C>
 __device__ __forceinline__ void pin_args(const Ptrs<N>& p, A a, B b, C c) {
@@ -434,6 +466,61 @@ __device__ __forceinline__ void reduce_ranks(const Ptrs<MAXP>& p, const RankTabl
                     }
                 }
         }
+    }
+}
+
+// Pointer of rank r from the rank table, r chosen per lane (all lanes active).
+__device__ __forceinline__ const uint4* lane_rank_in(const RankTable& tab, int r) {
+    const uint64_t lo = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(r * 4, static_cast<int>(tab.in_lo)));
+    const uint64_t hi = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(r * 4, static_cast<int>(tab.in_hi)));
+    return global_in((hi << 32) | lo);
+}
+
+__device__ __forceinline__ uint4* lane_rank_out(const RankTable& tab, int r) {
+    const uint64_t lo = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(r * 4, static_cast<int>(tab.out_lo)));
+    const uint64_t hi = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(r * 4, static_cast<int>(tab.out_hi)));
+    return global_out((hi << 32) | lo);
+}
+
+// Sum over ranks in ascending order of one element per lane, for the at most
+// 16 elements outside whole vectors: lanes 0 to 15 of a wave each ask for
+// element i and get its sum (lanes past the last element ask for it again).
+// PT > 0: every lane loads its element of every rank, all loads in flight.
+// Run-time counts: a rank's test around each load would end in a wait, so the
+// wave's 4 groups of 16 lanes load 4 ranks at a time, with no test (ranks past
+// the last load it again), and the sum takes the values from the lanes that
+// loaded them.  Called with every lane of the wave active and the wave's lanes
+// l and l + 16k asking for the same element.
+template <int PT, int DT, int MAXP>
+__device__ __forceinline__ float reduce_element(const Ptrs<MAXP>& p, const RankTable& tab, int P, int64_t i) {
+    using A = Arith<DT>;
+    using Raw = typename A::Raw;
+    if constexpr (PT > 0) {
+        Raw t[PT];
+#pragma unroll
+        for (int q = 0; q < PT; ++q) t[q] = reinterpret_cast<const Raw*>(p.in[q])[i];
+        float a = A::widen1(t[0]);
+#pragma unroll
+        for (int q = 1; q < PT; ++q) a = a + A::widen1(t[q]);
+        return a;
+    } else {
+        constexpr int kPasses = ((PT == 0 ? 64 : rank_cap<PT>()) + 3) / 4;
+        const RankTable ranks = PT == 0 ? tab : load_rank_table(p, P);
+        const int lane = threadIdx.x & 63;
+        float v[kPasses];
+#pragma unroll
+        for (int k = 0; k < kPasses; ++k) {
+            const int r = 4 * k + (lane >> 4);
+            v[k] = A::widen1(reinterpret_cast<const Raw*>(lane_rank_in(ranks, r < P ? r : P - 1))[i]);
+        }
+        float a = 0.0f;
+#pragma unroll
+        for (int r = 0; r < 4 * kPasses; ++r) {
+            const float x = __int_as_float(__builtin_amdgcn_ds_bpermute(((r & 3) * 16 + (lane & 15)) * 4,
+                                                                        __float_as_int(v[r >> 2])));
+            if (r < P) a = r == 0 ? x : a + x;
+        }
+        return a;
     }
 }
 

@@ -27,6 +27,29 @@ struct ArShape {
     int32_t gap;   // store_gap between destinations
 };
 
+// The `tail` (at most 7) elements after the last full vector, by one
+// workgroup: lanes 0 to 15 of its first wave sum and store them.
+template <int PT, int DT, int MAXP>
+__device__ __forceinline__ void tail_elements(const Ptrs<MAXP>& p, const RankTable& tab, int P, int64_t nvec,
+                                              int tail) {
+    using A = Arith<DT>;
+    if constexpr (PT > 0) {
+        if (static_cast<int>(threadIdx.x) < tail) {
+            const int64_t i = nvec * (16 / A::kEsize) + threadIdx.x;
+            const float a = reduce_element<PT, DT>(p, tab, P, i);
+            for (int d = 0; d < PT; ++d) A::store1(p.out[d], i, a);
+        }
+    } else if (threadIdx.x < 64) {
+        const int e = static_cast<int>(threadIdx.x & 15);
+        const int64_t i = nvec * (16 / A::kEsize) + (e < tail ? e : tail - 1);
+        const float a = reduce_element<PT, DT>(p, tab, P, i);
+        for (int d = 0; d < P; ++d) {
+            void* out = PT == 0 ? rank_out(tab, d) : p.out[d];
+            if (static_cast<int>(threadIdx.x) < tail) A::store1(out, i, a);
+        }
+    }
+}
+
 // WT: the item's stores use the system-scope cache policy (store_vecs_wt);
 // `cbase` is the chunk's first vector (v0 less the lane).
 template <int PT, int DT, int VPT, bool FULL, bool NT, bool WT, int MAXP>
@@ -61,7 +84,6 @@ __device__ __forceinline__ void allreduce_chunk(const Ptrs<MAXP>& p, const RankT
 
 template <int PT, int MAXP, int DT, int VPT, bool WT>
 __global__ __launch_bounds__(kWG) void k_allreduce(Ptrs<MAXP> p, ArShape s, Place pl) {
-    using A = Arith<DT>;
     const int nt = blockDim.x;
     const int64_t cv = static_cast<int64_t>(nt) * VPT;
     const int P = PT > 0 ? PT : s.P;
@@ -100,12 +122,7 @@ __global__ __launch_bounds__(kWG) void k_allreduce(Ptrs<MAXP> p, ArShape s, Plac
                 allreduce_chunk<PT, DT, VPT, false, false, false>(p, tab, s, P, v0, nt, g, all_dests, c * cv);
         }
     }
-    if (s.tail > 0 && blockIdx.x == 0 && static_cast<int>(threadIdx.x) < s.tail) {
-        const int64_t i = s.nvec * (16 / A::kEsize) + threadIdx.x;
-        float a = A::load1(p.in[0], i);
-        for (int r = 1; r < P; ++r) a = a + A::load1(p.in[r], i);
-        for (int d = 0; d < P; ++d) A::store1(p.out[d], i, a);
-    }
+    if (s.tail > 0 && blockIdx.x == 0) tail_elements<PT, DT>(p, tab, P, s.nvec, s.tail);
 }
 
 // Direct one-shot: one work item per workgroup (every uncapped launch whose
@@ -128,11 +145,14 @@ template <int PT, int DT, int VPT, bool WT>
 __global__ __launch_bounds__(kWG) void k_allreduce_direct(Ptrs<rank_cap<PT>()> p, int64_t nvec, int32_t tail,
                                                           int32_t gshift, int64_t nitems, int32_t gap,
                                                           int32_t ranks) {
-    using A = Arith<DT>;
     if constexpr (PT > 0)
         pin_args(p, nvec, tail, gshift, nitems, gap, blockDim.x);
     else
         pin_args(p, nvec, tail, gshift, nitems, gap, blockDim.x, ranks);
+    if constexpr (PT == -16) {
+        pin_inputs16(p);
+        pin_outputs16(p);
+    }
     const int P = PT > 0 ? PT : ranks;
     const int nt = blockDim.x;
     const int64_t cv = static_cast<int64_t>(nt) * VPT;
@@ -149,12 +169,7 @@ __global__ __launch_bounds__(kWG) void k_allreduce_direct(Ptrs<rank_cap<PT>()> p
         allreduce_chunk<PT, DT, VPT, true, true, WT>(p, tab, s, P, v0, nt, 0, true, c * cv);
     else
         allreduce_chunk<PT, DT, VPT, false, true, WT>(p, tab, s, P, v0, nt, 0, true, c * cv);
-    if (tail > 0 && blockIdx.x == 0 && static_cast<int>(threadIdx.x) < tail) {
-        const int64_t i = nvec * (16 / A::kEsize) + threadIdx.x;
-        float a = A::load1(p.in[0], i);
-        for (int r = 1; r < P; ++r) a = a + A::load1(p.in[r], i);
-        for (int d = 0; d < P; ++d) A::store1(p.out[d], i, a);
-    }
+    if (tail > 0 && blockIdx.x == 0) tail_elements<PT, DT>(p, tab, P, nvec, tail);
 }
 
 // ---------------------------------------------------------------- two-shot all-reduce, fused phases
@@ -338,7 +353,6 @@ __device__ __forceinline__ uint32_t lpr_sum_column(const uint32_t* col, int stri
 
 template <int PT, int DT>
 __global__ __launch_bounds__(kWG) void k_allreduce_lpr(Ptrs<64> p, LprShape s, Place pl) {
-    using A = Arith<DT>;
     extern __shared__ uint4 lds[];  // [P][V] tile, then [V] results
     const int P = PT > 0 ? PT : s.P;
     const int V = s.V;
@@ -374,12 +388,7 @@ __global__ __launch_bounds__(kWG) void k_allreduce_lpr(Ptrs<64> p, LprShape s, P
         if (active && vec < lim) store_stream(my_out + base + vec, res[vec]);
         __syncthreads();
     }
-    if (s.tail > 0 && blockIdx.x == 0 && t < s.tail) {
-        const int64_t e = s.nvec * (16 / A::kEsize) + t;
-        float a = A::load1(p.in[0], e);
-        for (int r = 1; r < P; ++r) a = a + A::load1(p.in[r], e);
-        for (int d = 0; d < P; ++d) A::store1(p.out[d], e, a);
-    }
+    if (s.tail > 0 && blockIdx.x == 0) tail_elements<0, DT>(p, tab, P, s.nvec, s.tail);
 }
 
 // ---------------------------------------------------------------- all-reduce, rank-major tiles (many ranks)
@@ -400,19 +409,6 @@ struct TileShape {
     int32_t P;
     int32_t tail;  // elements after the last full vector
 };
-
-// Pointer of rank r from the rank table, r chosen per lane (all lanes active).
-__device__ __forceinline__ const uint4* lane_rank_in(const RankTable& tab, int r) {
-    const uint64_t lo = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(r * 4, static_cast<int>(tab.in_lo)));
-    const uint64_t hi = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(r * 4, static_cast<int>(tab.in_hi)));
-    return global_in((hi << 32) | lo);
-}
-
-__device__ __forceinline__ uint4* lane_rank_out(const RankTable& tab, int r) {
-    const uint64_t lo = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(r * 4, static_cast<int>(tab.out_lo)));
-    const uint64_t hi = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(r * 4, static_cast<int>(tab.out_hi)));
-    return global_out((hi << 32) | lo);
-}
 
 // One work item of the tile kernel: V vectors of every rank starting at `base`.
 template <int PT, int DT, int V>
@@ -452,18 +448,6 @@ __device__ __forceinline__ void tile_item(const RankTable& tab, const TileShape&
     }
 }
 
-// Elements after the last full vector, summed by one workgroup.
-template <int DT, int MAXP>
-__device__ __forceinline__ void tail_elements(const Ptrs<MAXP>& p, int P, int64_t nvec, int tail) {
-    using A = Arith<DT>;
-    if (tail > 0 && blockIdx.x == 0 && static_cast<int>(threadIdx.x) < tail) {
-        const int64_t e = nvec * (16 / A::kEsize) + threadIdx.x;
-        float a = A::load1(p.in[0], e);
-        for (int r = 1; r < P; ++r) a = a + A::load1(p.in[r], e);
-        for (int d = 0; d < P; ++d) A::store1(p.out[d], e, a);
-    }
-}
-
 template <int PT, int DT, int V>
 __global__ __launch_bounds__(kWG) void k_allreduce_tile(Ptrs<64> p, TileShape s, Place pl) {
     static_assert(kWG % V == 0 && V * 4 <= kWG, "tile width");
@@ -477,7 +461,7 @@ __global__ __launch_bounds__(kWG) void k_allreduce_tile(Ptrs<64> p, TileShape s,
         tile_item<PT, DT, V>(tab, s, P, item_at(pl, blockIdx.x, gridDim.x, i) * V, lds);
         __syncthreads();
     }
-    tail_elements<DT>(p, P, s.nvec, s.tail);
+    if (s.tail > 0 && blockIdx.x == 0) tail_elements<PT, DT>(p, tab, P, s.nvec, s.tail);
 }
 
 // Direct tile kernel: one item per workgroup (every uncapped launch up to the
@@ -494,7 +478,7 @@ __global__ __launch_bounds__(kWG) void k_allreduce_tile_direct(Ptrs<64> p, TileS
     const int P = PT > 0 ? PT : s.P;
     const RankTable tab = load_rank_table(p, P);
     tile_item<PT, DT, V>(tab, s, P, item * V, lds);
-    tail_elements<DT>(p, P, s.nvec, s.tail);
+    if (s.tail > 0 && blockIdx.x == 0) tail_elements<PT, DT>(p, tab, P, s.nvec, s.tail);
 }
 
 // ---------------------------------------------------------------- launch helpers

@@ -247,7 +247,8 @@ __global__ __launch_bounds__(kWG) void k_combine_elem(Ptrs<64> p, const int64_t*
             float acc = 0.0f;
             for (int64_t e = e0; e < e1; ++e) {
                 const int2 q = ent[e];
-                float v = A::load1(p.in[q.x], static_cast<int64_t>(q.y) * rowelems + h);
+                float v = A::widen1(
+                    reinterpret_cast<const typename A::Raw*>(p.in[q.x])[static_cast<int64_t>(q.y) * rowelems + h]);
                 if (wts) v = wts[static_cast<int64_t>(tok) * P + q.x] * v;
                 acc = e == e0 ? v : acc + v;
             }

@@ -77,6 +77,7 @@ __global__ __launch_bounds__(kWG) void k_reduce_scatter_direct(Ptrs<rank_cap<PT>
         pin_args(p, mv, blockDim.x, blockIdx.y);
     else
         pin_args(p, mv, blockDim.x, blockIdx.y, ranks);
+    if constexpr (PT == -16) pin_inputs16(p);
     const int nt = blockDim.x;
     const int64_t cv = static_cast<int64_t>(nt) * VPT;
     const int64_t c = blockIdx.x;
@@ -93,16 +94,171 @@ __global__ __launch_bounds__(kWG) void k_reduce_scatter_direct(Ptrs<rank_cap<PT>
         reduce_scatter_chunk<PT, DT, VPT, false, KEEP, N, (N <= 8)>(p, tab, s, P, r, v0, nt);
 }
 
-// Element-wise fallback when a shard is not a whole number of 16-byte vectors.
-template <int DT>
-__global__ __launch_bounds__(kWG) void k_reduce_scatter_elem(Ptrs<64> p, int P, int64_t m) {
+// ---------------------------------------------------------------- ragged shards
+//
+// Shards that are no whole number of 16-byte vectors: shard r of a buffer
+// then begins off a vector boundary.  The stores decide the cut, since they
+// want whole aligned vectors: a shard's destination is `head` bytes up to the
+// first boundary, `nv` aligned vectors, and the bytes after the last one.  The
+// vectors are loaded from wherever they start in the source (load16_any).
+// They are numbered from the 128-byte line the first one lies in (`lead`
+// vectors into it), so that every wave but the first and last writes whole
+// lines: with waves starting inside a line, their streamed partial lines cost
+// the all-gather a third of its rate (8 ranks of bf16, 2 MiB shards: 35.1 us
+// against 25.9 for aligned shards).  The head and tail, at most 14 elements,
+// are moved element by element by one more workgroup per shard, so that no
+// chunk waits for them.
+// An element per thread with a 64-bit division for its shard, which now serves
+// the small shards only (below), took 15.4 us for the reduce-scatter of 8 ranks of bf16 at 512 KiB shards (now
+// 8.0) and 55.1 us for the all-gather at 2 MiB shards (24.2).
+constexpr int kLineVecs = 8;  // 16-byte vectors in a 128-byte line
+
+struct RaggedCut {
+    int64_t head;  // bytes before the first aligned vector (at most the shard)
+    int64_t nv;    // aligned vectors
+    int64_t lead;  // vectors of the first one's line that come before it
+    int64_t tail;  // bytes after the last vector
+};
+
+__device__ __forceinline__ RaggedCut ragged_cut(uint64_t dst, int64_t bytes) {
+    RaggedCut k;
+    const int64_t to = static_cast<int64_t>((0 - dst) & 15u);
+    k.head = to < bytes ? to : bytes;
+    k.nv = (bytes - k.head) >> 4;
+    k.lead = static_cast<int64_t>(((dst + k.head) >> 4) & (kLineVecs - 1));
+    k.tail = (bytes - k.head) & 15;
+    return k;
+}
+
+// Host: chunks of cv vectors that cover a shard of mv vectors and its lead.
+inline int64_t ragged_chunks(int64_t mv, int64_t cv) { return mv > 0 ? (mv + kLineVecs - 1 + cv - 1) / cv : 0; }
+
+// Byte offset of edge element e (head elements first), or -1 past the last.
+template <int ES>
+__device__ __forceinline__ int64_t edge_offset(const RaggedCut& k, int e) {
+    const int64_t at = static_cast<int64_t>(e) * ES;
+    if (at < k.head) return at;
+    return at < k.head + k.tail ? at + k.nv * 16 : -1;
+}
+
+// acc[j] = sum over ranks in ascending order of the 16 bytes at off + 16 * (v0 + j*nt) of every
+// input, for vectors from 0 to below `limit` (at least 1).  Lanes outside load the nearest vector
+// inside and are never stored: a masked load would put a branch and its wait into every rank's test.
+template <int PT, int DT, int VPT, bool FULL, int MAXP>
+__device__ __forceinline__ void reduce_ranks_any(const Ptrs<MAXP>& p, const RankTable& tab, int P, int64_t off,
+                                                 int64_t v0, int nt, int64_t limit,
+                                                 float (&acc)[VPT][Arith<DT>::kLanes]) {
     using A = Arith<DT>;
+    constexpr int B = rank_batch<PT>();
+    for (int r0 = 0; r0 < (PT != 0 ? 1 : P); r0 += B) {
+        uint4 buf[B][VPT];
+#pragma unroll
+        for (int q = 0; q < B; ++q)
+            if (PT > 0 || r0 + q < P) {
+                const char* src = reinterpret_cast<const char*>(in_ptr<PT>(p, tab, r0 + q)) + off;
+#pragma unroll
+                for (int j = 0; j < VPT; ++j) {
+                    int64_t v = v0 + j * nt;
+                    if (!FULL) v = v < 0 ? 0 : v < limit ? v : limit - 1;
+                    buf[q][j] = load16_any<false>(src + v * 16);
+                }
+            }
+#pragma unroll
+        for (int q = 0; q < B; ++q)
+            if (PT > 0 || r0 + q < P) {
+#pragma unroll
+                for (int j = 0; j < VPT; ++j) {
+                    if (r0 + q == 0)
+                        A::init(acc[j], buf[q][j]);
+                    else
+                        A::add(acc[j], buf[q][j]);
+                }
+            }
+    }
+}
+
+// Vectors within [0, limit) of a chunk's, to a destination that starts at vector 0.
+template <bool FULL, int VPT, bool NT>
+__device__ __forceinline__ void store_range(uint4* dst, const uint4 (&y)[VPT], int64_t v0, int nt, int64_t limit) {
+#pragma unroll
+    for (int j = 0; j < VPT; ++j) {
+        if (FULL || (v0 + j * nt >= 0 && v0 + j * nt < limit)) {
+            if constexpr (NT)
+                store_stream(dst + v0 + j * nt, y[j]);
+            else
+                dst[v0 + j * nt] = y[j];
+        }
+    }
+}
+
+// Workgroup (c, r) reduces chunk c of shard r, c = wcs its edge elements (a
+// capped grid walks on by the grid's size).  m elements per shard; the output
+// pointer may sit at any element (a two-shot's shard inside an output).
+template <int PT, int DT, int VPT, bool KEEP, int MAXP>
+__global__ __launch_bounds__(kWG) void k_reduce_scatter_ragged(Ptrs<MAXP> p, int64_t m, int64_t wcs, int32_t ranks) {
+    using A = Arith<DT>;
+    if constexpr (PT != 0) pin_args(p, m, wcs, ranks, blockDim.x);
+    if constexpr (PT == -16) pin_inputs16(p);
+    const int P = PT > 0 ? PT : ranks;
+    const RankTable tab = use_table<PT>() ? load_rank_table(p, P) : RankTable{0u, 0u, 0u, 0u};
+    const int nt = blockDim.x;
+    const int64_t cv = static_cast<int64_t>(nt) * VPT;
+    for (int r = static_cast<int>(blockIdx.y); r < P; r += static_cast<int>(gridDim.y)) {
+        char* dst;
+        if constexpr (use_table<PT>())
+            dst = reinterpret_cast<char*>(rank_out(tab, r));
+        else if constexpr (MAXP <= 8)
+            dst = reinterpret_cast<char*>(out_at(p, r));
+        else
+            dst = reinterpret_cast<char*>(p.out[r]);
+        const int64_t bytes = m * A::kEsize;
+        const RaggedCut k = ragged_cut(reinterpret_cast<uint64_t>(dst), bytes);
+        const int64_t off = r * bytes + k.head;
+        uint4* out = reinterpret_cast<uint4*>(dst + k.head);
+        for (int64_t c = blockIdx.x; c <= wcs; c += gridDim.x) {
+            if (c == wcs) {
+                if (threadIdx.x < 64) {  // one wave; lanes without an element take the shard's first
+                    const int64_t at = edge_offset<A::kEsize>(k, static_cast<int>(threadIdx.x & 15));
+                    const float a = reduce_element<PT, DT>(p, tab, P, (r * bytes + (at < 0 ? 0 : at)) / A::kEsize);
+                    if (at >= 0 && threadIdx.x < 16) A::store1(dst, at / A::kEsize, a);
+                }
+                break;
+            }
+            const int64_t v0 = c * cv - k.lead + threadIdx.x;
+            float acc[VPT][A::kLanes];
+            uint4 y[VPT];
+            if (c * cv >= k.lead && (c + 1) * cv - k.lead <= k.nv) {
+                reduce_ranks_any<PT, DT, VPT, true>(p, tab, P, off, v0, nt, k.nv, acc);
+#pragma unroll
+                for (int j = 0; j < VPT; ++j) y[j] = A::narrow(acc[j]);
+                store_range<true, VPT, !KEEP>(out, y, v0, nt, k.nv);
+            } else if (k.nv > 0) {
+                reduce_ranks_any<PT, DT, VPT, false>(p, tab, P, off, v0, nt, k.nv, acc);
+#pragma unroll
+                for (int j = 0; j < VPT; ++j) y[j] = A::narrow(acc[j]);
+                store_range<false, VPT, !KEEP>(out, y, v0, nt, k.nv);
+            }
+        }
+    }
+}
+
+// Element by element, for small ragged shards of run-time rank counts: the
+// kernel above tests for every rank there, and its longer code costs more than
+// its wide loads save up to 512 Ki elements of input per rank (6 ranks of bf16:
+// 2.3 against 2.7 us at 16 KiB shards, 10.1 against 6.4 at 512 KiB; 12 ranks of
+// fp32 6.3 against 6.7 at 128 KiB, 19.6 against 15.7 at 512 KiB).
+constexpr int64_t kRsRaggedElems = int64_t(1) << 19;
+
+template <int DT>
+__global__ __launch_bounds__(kWG) void k_reduce_scatter_elem(Ptrs<16> p, int P, int64_t m) {
+    using A = Arith<DT>;
+    using Raw = typename A::Raw;
     const int64_t total = m * P;
     for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < total;
          i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
         const int64_t r = i / m;
-        float a = A::load1(p.in[0], i);
-        for (int q = 1; q < P; ++q) a = a + A::load1(p.in[q], i);
+        float a = A::widen1(reinterpret_cast<const Raw*>(p.in[0])[i]);
+        for (int q = 1; q < P; ++q) a = a + A::widen1(reinterpret_cast<const Raw*>(p.in[q])[i]);
         A::store1(p.out[r], i - r * m, a);
     }
 }
@@ -184,6 +340,7 @@ __global__ __launch_bounds__(kWG) void k_all_gather_direct(Ptrs<rank_cap<PT>()> 
         pin_args(p, mv, gap, blockDim.x);
     else
         pin_args(p, mv, gap, blockDim.x, ranks);
+    if constexpr (PT == -16) pin_outputs16(p);
     const int nt = blockDim.x;
     const int64_t cv = static_cast<int64_t>(nt) * VPT;
     const int64_t c = blockIdx.x;
@@ -216,8 +373,15 @@ __global__ __launch_bounds__(kWG) void k_all_gather_direct(Ptrs<rank_cap<PT>()> 
     }
 }
 
+// Element by element, for up to 8 ranks and 512 Ki elements of output, where the
+// kernel below is the slower one (fewer waves in flight for the same bytes): 8
+// ranks of bf16 at 32 KiB shards 2.46 against 2.66 us and at 64 KiB 2.92 against
+// 3.31, 4 ranks at 128 KiB 2.31 against 2.72; at 128 KiB shards and 8 ranks 4.18
+// against 3.79.
+constexpr int64_t kAgRaggedElems = int64_t(1) << 19;
+
 template <int ES>
-__global__ __launch_bounds__(kWG) void k_all_gather_elem(Ptrs<64> p, int P, int64_t m) {
+__global__ __launch_bounds__(kWG) void k_all_gather_elem(Ptrs<8> p, int P, int64_t m) {
     using E = typename std::conditional<ES == 2, uint16_t, uint32_t>::type;
     const int64_t total = m * P;
     for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < total;
@@ -229,6 +393,82 @@ __global__ __launch_bounds__(kWG) void k_all_gather_elem(Ptrs<64> p, int P, int6
         for (int d = 0; d < P; ++d) {
             E* dst = reinterpret_cast<E*>(p.out[d]) + r * m;
             if (dst != src) dst[j] = v;
+        }
+    }
+}
+
+// All-gather of ragged shards: workgroup (c, r, g) copies chunk c of shard r,
+// c = wcs its edge elements, to the destinations [g * dpi, (g + 1) * dpi).
+// `bytes` per shard.
+template <int PT, int ES, int VPT, int MAXP>
+__global__ __launch_bounds__(kWG) void k_all_gather_ragged(Ptrs<MAXP> p, int64_t bytes, int64_t wcs, int32_t ranks,
+                                                           int32_t dpi, int32_t gap) {
+    using E = typename std::conditional<ES == 2, uint16_t, uint32_t>::type;
+    if constexpr (PT != 0) pin_args(p, bytes, wcs, ranks, dpi, gap, blockDim.x);
+    const int P = PT > 0 ? PT : ranks;
+    const RankTable tab = use_table<PT>() ? load_rank_table(p, P) : RankTable{0u, 0u, 0u, 0u};
+    const int nt = blockDim.x;
+    const int64_t cv = static_cast<int64_t>(nt) * VPT;
+    const int d0 = static_cast<int>(blockIdx.z) * dpi;
+    const int d1 = d0 + dpi < P ? d0 + dpi : P;
+    // The outputs' place within a line (any of them: it changes no result).
+    const uint64_t out0 = reinterpret_cast<uint64_t>(out_ptr<PT>(p, tab, 0));
+    auto each_destination = [&](auto&& put) {
+        if constexpr (use_table<PT>()) {
+            for (int d = d0; d < d1; ++d) {
+                if (d > d0) store_gap(gap);
+                put(reinterpret_cast<char*>(rank_out(tab, d)));
+            }
+        } else {
+#pragma unroll
+            for (int d = 0; d < rank_cap<PT>(); ++d)
+                if (d >= d0 && d < d1) {
+                    if (d > d0) store_gap(gap);
+                    put(reinterpret_cast<char*>(p.out[d]));
+                }
+        }
+    };
+    for (int r = static_cast<int>(blockIdx.y); r < P; r += static_cast<int>(gridDim.y)) {
+        const char* src;
+        if constexpr (use_table<PT>())
+            src = reinterpret_cast<const char*>(rank_in(tab, r));
+        else if constexpr (MAXP <= 8)
+            src = reinterpret_cast<const char*>(in_at(p, r));
+        else
+            src = reinterpret_cast<const char*>(p.in[r]);
+        const int64_t base = r * bytes;
+        const RaggedCut k = ragged_cut(out0 + static_cast<uint64_t>(base), bytes);
+        for (int64_t c = blockIdx.x; c <= wcs; c += gridDim.x) {
+            if (c == wcs) {
+                const int64_t at = edge_offset<ES>(k, static_cast<int>(threadIdx.x));
+                const E edge = at >= 0 ? *reinterpret_cast<const E*>(src + at) : E(0);
+                each_destination([&](char* out) {
+                    char* dst = out + base;
+                    if (dst != src && at >= 0) *reinterpret_cast<E*>(dst + at) = edge;
+                });
+                break;
+            }
+            const int64_t v0 = c * cv - k.lead + threadIdx.x;
+            const char* from = src + k.head;
+            uint4 y[VPT];
+            if (c * cv >= k.lead && (c + 1) * cv - k.lead <= k.nv) {
+#pragma unroll
+                for (int j = 0; j < VPT; ++j) y[j] = load16_any<false>(from + (v0 + j * nt) * 16);
+                each_destination([&](char* out) {
+                    char* dst = out + base;
+                    if (dst != src)  // else an in-place shard
+                        store_range<true, VPT, true>(reinterpret_cast<uint4*>(dst + k.head), y, v0, nt, k.nv);
+                });
+            } else {
+#pragma unroll
+                for (int j = 0; j < VPT; ++j)
+                    if (v0 + j * nt >= 0 && v0 + j * nt < k.nv) y[j] = load16_any<false>(from + (v0 + j * nt) * 16);
+                each_destination([&](char* out) {
+                    char* dst = out + base;
+                    if (dst != src)
+                        store_range<false, VPT, true>(reinterpret_cast<uint4*>(dst + k.head), y, v0, nt, k.nv);
+                });
+            }
         }
     }
 }
@@ -302,22 +542,100 @@ void launch_rs(bool direct, const void* const* in, void* const* out, const RsSha
     else vpt == 4 ? go(Bf16{}, V4{}) : vpt == 2 ? go(Bf16{}, V2{}) : go(Bf16{}, V1{});
 }
 
+// Grid of a ragged launch: (chunks and edges, shards, destination groups), cut down to
+// the workgroup cap; the kernels walk on over chunks and shards.
+dim3 ragged_grid(int64_t wcs, int P, int groups) {
+    ++wcs;  // and the edges
+    const int64_t cap = max_workgroups() / groups > 0 ? max_workgroups() / groups : 1;
+    const int64_t y = P < cap ? P : cap;
+    const int64_t x = wcs < cap / y ? wcs : cap / y;
+    return dim3(static_cast<unsigned>(x > 0 ? x : 1), static_cast<unsigned>(y), static_cast<unsigned>(groups));
+}
+
+template <int PT, int DT, int VPT, bool KEEP>
+void launch_rs_ragged_t(const void* const* in, void* const* out, int P, int64_t m, int64_t wcs, int nt,
+                        hipStream_t st) {
+    constexpr int N = PT == 0 ? 64 : rank_cap<PT>();
+    const auto p = make_ptrs<N>(in, out, P, P);
+    hipLaunchKernelGGL((k_reduce_scatter_ragged<PT, DT, VPT, KEEP, N>), ragged_grid(wcs, P, 1), dim3(nt), 0, st, p, m,
+                       wcs, P);
+}
+
+template <int DT, int VPT, bool KEEP>
+void launch_rs_ragged_p(const void* const* in, void* const* out, int P, int64_t m, int64_t wcs, int nt,
+                        hipStream_t st) {
+    if (P > 16) launch_rs_ragged_t<0, DT, 1, KEEP>(in, out, P, m, wcs, nt, st);
+    else if (P == 16) launch_rs_ragged_t<16, DT, VPT, KEEP>(in, out, P, m, wcs, nt, st);
+    else if (P > 8) launch_rs_ragged_t<-16, DT, VPT, KEEP>(in, out, P, m, wcs, nt, st);
+    else if (P == 8) launch_rs_ragged_t<8, DT, VPT, KEEP>(in, out, P, m, wcs, nt, st);
+    else if (P > 4) launch_rs_ragged_t<-8, DT, VPT, KEEP>(in, out, P, m, wcs, nt, st);
+    else if (P == 2) launch_rs_ragged_t<2, DT, VPT, KEEP>(in, out, P, m, wcs, nt, st);
+    else launch_rs_ragged_t<-4, DT, VPT, KEEP>(in, out, P, m, wcs, nt, st);
+}
+
+template <bool KEEP>
+void launch_rs_ragged(const void* const* in, void* const* out, int P, int64_t m, int64_t wcs, int dtype, int vpt,
+                      int nt, hipStream_t st) {
+    if (dtype == kDtF32) {
+        if (vpt == 4) launch_rs_ragged_p<kDtF32, 4, KEEP>(in, out, P, m, wcs, nt, st);
+        else if (vpt == 2) launch_rs_ragged_p<kDtF32, 2, KEEP>(in, out, P, m, wcs, nt, st);
+        else launch_rs_ragged_p<kDtF32, 1, KEEP>(in, out, P, m, wcs, nt, st);
+    } else {
+        if (vpt == 4) launch_rs_ragged_p<kDtBf16, 4, KEEP>(in, out, P, m, wcs, nt, st);
+        else if (vpt == 2) launch_rs_ragged_p<kDtBf16, 2, KEEP>(in, out, P, m, wcs, nt, st);
+        else launch_rs_ragged_p<kDtBf16, 1, KEEP>(in, out, P, m, wcs, nt, st);
+    }
+}
+
+template <int PT, int ES, int VPT>
+void launch_ag_ragged_t(const void* const* in, void* const* out, int P, int64_t bytes, int64_t wcs, int nt, int dpi,
+                        int gap, hipStream_t st) {
+    constexpr int N = PT == 0 ? 64 : rank_cap<PT>();
+    const auto p = make_ptrs<N>(in, out, P, P);
+    hipLaunchKernelGGL((k_all_gather_ragged<PT, ES, VPT, N>), ragged_grid(wcs, P, (P + dpi - 1) / dpi), dim3(nt), 0,
+                       st, p, bytes, wcs, P, dpi, gap);
+}
+
+template <int ES, int VPT>
+void launch_ag_ragged(const void* const* in, void* const* out, int P, int64_t bytes, int64_t wcs, int nt, int dpi,
+                      int gap, hipStream_t st) {
+    // Split destinations: the rank table's loop runs the group's few stores only.
+    if (P > 8 || (dpi < P && P > 4)) launch_ag_ragged_t<0, ES, VPT>(in, out, P, bytes, wcs, nt, dpi, gap, st);
+    else if (P == 8) launch_ag_ragged_t<8, ES, VPT>(in, out, P, bytes, wcs, nt, dpi, gap, st);
+    else if (P > 4) launch_ag_ragged_t<-8, ES, VPT>(in, out, P, bytes, wcs, nt, dpi, gap, st);
+    else launch_ag_ragged_t<-4, ES, VPT>(in, out, P, bytes, wcs, nt, dpi, gap, st);
+}
+
 }  // namespace
 
 hipError_t launch_reduce_scatter(const void* const* in, void* const* out, int P, size_t m, int dtype, int mode,
                                  bool keep_output, hipStream_t stream) {
     const size_t es = dtype_size(dtype);
     if ((m * es) % 16 != 0) {
-        Ptrs<64> p = make_ptrs<64>(in, out, P, P);
+        const int64_t mv = static_cast<int64_t>(m * es / 16);
         const int64_t total = static_cast<int64_t>(m) * P;
-        const int64_t G = cap_grid((total + kWG - 1) / kWG);
-        note_launch("k_reduce_scatter_elem", kMapLinear, 1, G, kWG, 0);
-        if (dtype == kDtF32)
-            hipLaunchKernelGGL((k_reduce_scatter_elem<kDtF32>), dim3(static_cast<unsigned>(G)), dim3(kWG), 0, stream,
-                               p, P, static_cast<int64_t>(m));
-        else
-            hipLaunchKernelGGL((k_reduce_scatter_elem<kDtBf16>), dim3(static_cast<unsigned>(G)), dim3(kWG), 0, stream,
-                               p, P, static_cast<int64_t>(m));
+        if (P < 16 && P != 2 && P != 8 && total <= kRsRaggedElems) {
+            const Ptrs<16> p = make_ptrs<16>(in, out, P, P);
+            const int64_t G = cap_grid((total + kWG - 1) / kWG);
+            note_launch("k_reduce_scatter_elem", kMapLinear, 1, G, kWG, 0);
+            if (dtype == kDtF32)
+                hipLaunchKernelGGL((k_reduce_scatter_elem<kDtF32>), dim3(static_cast<unsigned>(G)), dim3(kWG), 0,
+                                   stream, p, P, static_cast<int64_t>(m));
+            else
+                hipLaunchKernelGGL((k_reduce_scatter_elem<kDtBf16>), dim3(static_cast<unsigned>(G)), dim3(kWG), 0,
+                                   stream, p, P, static_cast<int64_t>(m));
+            return hipGetLastError();
+        }
+        int nt, vpt;
+        pick_rs_shape(mv * P, P, dtype, nt, vpt);
+        if (P > 16) vpt = 1;
+        if (vpt == 1 && !tuning().wg_threads) nt = 64;  // more workgroups for the small sizes
+        const int64_t cv = static_cast<int64_t>(nt) * vpt;
+        const int64_t wcs = ragged_chunks(mv, cv);
+        const dim3 g = ragged_grid(wcs, P, 1);
+        note_launch("k_reduce_scatter_ragged", kMapLinear, 1, int64_t(g.x) * g.y, nt, vpt);
+        if (keep_output) launch_rs_ragged<true>(in, out, P, static_cast<int64_t>(m), wcs, dtype, vpt, nt, stream);
+        else launch_rs_ragged<false>(in, out, P, static_cast<int64_t>(m), wcs, dtype, vpt, nt, stream);
         return hipGetLastError();
     }
     RsShape s{};
@@ -362,16 +680,39 @@ hipError_t launch_all_gather(const void* const* in, void* const* out, int P, siz
                              bool src_cached, hipStream_t stream) {
     const size_t es = dtype_size(dtype);
     if ((m * es) % 16 != 0) {
-        Ptrs<64> p = make_ptrs<64>(in, out, P, P);
-        const int64_t total = static_cast<int64_t>(m) * P;
-        const int64_t G = cap_grid((total + kWG - 1) / kWG);
-        note_launch("k_all_gather_elem", kMapLinear, 1, G, kWG, 0);
-        if (es == 4)
-            hipLaunchKernelGGL((k_all_gather_elem<4>), dim3(static_cast<unsigned>(G)), dim3(kWG), 0, stream, p, P,
-                               static_cast<int64_t>(m));
-        else
-            hipLaunchKernelGGL((k_all_gather_elem<2>), dim3(static_cast<unsigned>(G)), dim3(kWG), 0, stream, p, P,
-                               static_cast<int64_t>(m));
+        const int64_t bytes = static_cast<int64_t>(m * es), mv = bytes / 16, total = static_cast<int64_t>(m) * P;
+        if (P <= 8 && total <= kAgRaggedElems) {
+            const Ptrs<8> p = make_ptrs<8>(in, out, P, P);
+            const int64_t G = cap_grid((total + kWG - 1) / kWG);
+            note_launch("k_all_gather_elem", kMapLinear, 1, G, kWG, 0);
+            if (es == 4)
+                hipLaunchKernelGGL((k_all_gather_elem<4>), dim3(static_cast<unsigned>(G)), dim3(kWG), 0, stream, p, P,
+                                   static_cast<int64_t>(m));
+            else
+                hipLaunchKernelGGL((k_all_gather_elem<2>), dim3(static_cast<unsigned>(G)), dim3(kWG), 0, stream, p, P,
+                                   static_cast<int64_t>(m));
+            return hipGetLastError();
+        }
+        int nt, vpt;
+        pick_ag_shape(mv * P, P, nt, vpt);
+        const int64_t cv = static_cast<int64_t>(nt) * vpt;
+        const int64_t wcs = ragged_chunks(mv, cv);
+        // Up to 4 groups while the launch is short of 1500 workgroups: 8 ranks of 128 KiB
+        // shards 3.98 us against 4.73 with 8 groups and 4.60 with one.
+        const int split = wcs * P < 1500 ? largest_divisor_upto(P, 4) : 1;
+        const int groups = split <= max_workgroups() ? split : 1;
+        const int dpi = P / groups, gap = store_gap_for(m * es * P);
+        const dim3 g = ragged_grid(wcs, P, groups);
+        note_launch("k_all_gather_ragged", kMapLinear, 1, int64_t(g.x) * g.y * g.z, nt, vpt);
+        if (es == 4) {
+            if (vpt == 4) launch_ag_ragged<4, 4>(in, out, P, bytes, wcs, nt, dpi, gap, stream);
+            else if (vpt == 2) launch_ag_ragged<4, 2>(in, out, P, bytes, wcs, nt, dpi, gap, stream);
+            else launch_ag_ragged<4, 1>(in, out, P, bytes, wcs, nt, dpi, gap, stream);
+        } else {
+            if (vpt == 4) launch_ag_ragged<2, 4>(in, out, P, bytes, wcs, nt, dpi, gap, stream);
+            else if (vpt == 2) launch_ag_ragged<2, 2>(in, out, P, bytes, wcs, nt, dpi, gap, stream);
+            else launch_ag_ragged<2, 1>(in, out, P, bytes, wcs, nt, dpi, gap, stream);
+        }
         return hipGetLastError();
     }
     AgShape s{};

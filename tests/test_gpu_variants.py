@@ -145,3 +145,54 @@ def test_reduce_scatter_shape_edges(nuna, P, quarter):
         got = _run(nuna.reduce_scatter, x, mv * 4, f"P={P} mv={mv}")
         for r in (0, P - 1):
             assert_bitwise(got[r], ref[r], f"P={P} mv={mv} rank {r}")
+
+
+# ---------------------------------------------------------------- ragged shards
+
+@pytest.mark.parametrize("P", [2, 3, 5, 8, 11, 16, 20, 64])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_ragged_shards(nuna, P, dtype):
+    """Shards of every remainder of a vector, below one vector, around chunk edges and at several vectors
+    per thread: reduce-scatter, all-gather, and the two-shot in place (whose shards begin at any element)."""
+    lanes = 8 if dtype == "bf16" else 4
+    big = (1 << 19) // P // (4 if P > 16 else 1)
+    big = max(big, 3 * (1 << 16) // P)
+    sizes = [1, 2, lanes - 1, lanes + 1] + [64 * lanes + e for e in range(1, lanes)] + \
+        [256 * lanes - 1, 256 * lanes + 1, big * lanes // 4 + 3, big * lanes // 2 + 1]
+    for k, m in enumerate(sizes):
+        what = f"P={P} {dtype} m={m}"
+        x = _values(P, P * m, dtype, 43 * P + k)
+        ref = oracle.reduce_scatter(x)
+        got = _run(nuna.reduce_scatter, x, m, "RS " + what)
+        src = [a[:m].copy() for a in x]
+        ref_g = oracle.all_gather(src)
+        got_g = _run(nuna.all_gather, src, P * m, "AG " + what)
+        ref_a = oracle.allreduce(x)
+        bufs = [to_dev(a) for a in x]
+        nuna.allreduce(bufs, bufs, algo="two_shot_two_kernels")
+        torch.cuda.synchronize()
+        for d in range(P):
+            assert_bitwise(got[d], ref[d], f"RS {what} rank {d}")
+        for d in {0, P // 2, P - 1}:
+            assert_bitwise(got_g[d], ref_g[d], f"AG {what} rank {d}")
+            assert_bitwise(to_host(bufs[d]), ref_a[d], f"two-shot {what} rank {d}")
+
+
+@pytest.mark.parametrize("cap", [1, 3, 40])
+def test_ragged_shards_under_a_workgroup_cap(nuna, cap):
+    """A capped launch walks on over chunks and shards, with no more workgroups than the cap."""
+    P, m = 6, 5003
+    x = _values(P, P * m, "bf16", 5)
+    src = [a[:m].copy() for a in x]
+    nuna.set_max_workgroups(cap)
+    try:
+        got = _run(nuna.reduce_scatter, x, m, "RS")
+        assert nuna.last_launch()["grid"] <= cap
+        got_g = _run(nuna.all_gather, src, P * m, "AG")
+        assert nuna.last_launch()["grid"] <= cap
+    finally:
+        nuna.set_max_workgroups(0)
+    ref, ref_g = oracle.reduce_scatter(x), oracle.all_gather(src)
+    for d in range(P):
+        assert_bitwise(got[d], ref[d], f"RS rank {d}")
+        assert_bitwise(got_g[d], ref_g[d], f"AG rank {d}")
