@@ -542,5 +542,20 @@ inline int64_t cap_grid(int64_t wgs) {
     return wgs < cap ? (wgs > 0 ? wgs : 1) : cap;
 }
 
+// One row of rowvec 16-byte vectors, by NT threads.  Loads go through the caches
+// (a row is read once per destination); stores stream.
+template <int NT, int VPT>
+__device__ __forceinline__ void copy_row(const uint4* src, uint4* dst, int64_t rowvec, int tid) {
+    for (int64_t v = tid; v < rowvec; v += NT * VPT) {
+        uint4 y[VPT];
+#pragma unroll
+        for (int u = 0; u < VPT; ++u)
+            if (v + u * NT < rowvec) y[u] = src[v + u * NT];
+#pragma unroll
+        for (int u = 0; u < VPT; ++u)
+            if (v + u * NT < rowvec) store_stream(dst + v + u * NT, y[u]);
+    }
+}
+
 }  // namespace
 }  // namespace nuna

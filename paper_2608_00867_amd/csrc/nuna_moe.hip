@@ -7,6 +7,7 @@
 // (rank, row) lists: fixed-size records with up to 8 ranks, offset lists
 // beyond.  No MFMA: rows are moved and added, never contracted.
 #include "device_common.h"
+#include "shapes.h"
 
 namespace nuna {
 namespace {
@@ -15,11 +16,10 @@ namespace {
 
 // One descriptor per row copy, stored in placement order: source rank,
 // source token, destination rank, destination row.
-template <int MAXP, int UNROLL>
-__global__ __launch_bounds__(kWG) void k_all_to_all(Ptrs<MAXP> p, int P, const int4* __restrict__ desc,
+template <int MAXP, int NT>
+__global__ __launch_bounds__(NT) void k_all_to_all(Ptrs<MAXP> p, int P, const int4* __restrict__ desc,
                                                     int64_t rowvec, Place pl) {
     // The dispatch always runs per-XCD item lists (Place gsize 0).
-    const int nt = blockDim.x;
     const RankTable tab = load_rank_table(p, P);
     // The scalar arguments the item loop needs go into one empty statement, so
     // their loads issue together instead of one after another.  The list
@@ -29,22 +29,14 @@ __global__ __launch_bounds__(kWG) void k_all_to_all(Ptrs<MAXP> p, int P, const i
     // then no longer be scalar loads.
     const int x = static_cast<int>(blockIdx.x & (kNumXcd - 1));
     int64_t lo = pl.start[x], hi = pl.start[x + 1], total = pl.start[kNumXcd];
-    asm("" : "+s"(lo), "+s"(hi), "+s"(total) : "s"(rowvec), "s"(pl.mode), "s"(blockDim.x), "s"(gridDim.x));
+    asm("" : "+s"(lo), "+s"(hi), "+s"(total) : "s"(rowvec), "s"(pl.mode), "s"(gridDim.x));
     const bool linear = pl.mode == kPlaceLinear || gridDim.x < kNumXcd;
     const ItemRange it = list_items(linear, lo, hi, total, blockIdx.x, gridDim.x);
     for (int64_t i = it.first; i < it.end; i += it.stride) {
         const int4 d = desc[i];
         const uint4* src = rank_in(tab, d.x) + static_cast<int64_t>(d.y) * rowvec;
         uint4* dst = rank_out(tab, d.z) + static_cast<int64_t>(d.w) * rowvec;
-        for (int64_t v = threadIdx.x; v < rowvec; v += static_cast<int64_t>(nt) * UNROLL) {
-            uint4 y[UNROLL];
-#pragma unroll
-            for (int u = 0; u < UNROLL; ++u)
-                if (v + u * nt < rowvec) y[u] = src[v + u * nt];
-#pragma unroll
-            for (int u = 0; u < UNROLL; ++u)
-                if (v + u * nt < rowvec) store_stream(dst + v + u * nt, y[u]);
-        }
+        copy_row<NT, kRowVpt>(src, dst, rowvec, static_cast<int>(threadIdx.x));
     }
 }
 
@@ -306,6 +298,18 @@ void launch_combine_w(const void* const* y, void* const* out, int P, const int64
 
 }  // namespace
 
+template <int NT>
+void launch_a2a(const void* const* send, void* const* recv, int P, const int4* d, int64_t rowvec, const Place& pl,
+                int64_t G, hipStream_t stream) {
+    const dim3 grid(static_cast<unsigned>(G)), block(NT);
+    if (P <= 8)
+        hipLaunchKernelGGL((k_all_to_all<8, NT>), grid, block, 0, stream, make_ptrs<8>(send, recv, P, P), P, d,
+                           rowvec, pl);
+    else
+        hipLaunchKernelGGL((k_all_to_all<64, NT>), grid, block, 0, stream, make_ptrs<64>(send, recv, P, P), P, d,
+                           rowvec, pl);
+}
+
 hipError_t launch_all_to_all(const void* const* send, void* const* recv, int P, const void* desc, int64_t nitems,
                              const int64_t* xcd_start, size_t row_bytes, int esize, int mode, hipStream_t stream) {
     const bool vec = row_bytes % 16 == 0;
@@ -331,18 +335,11 @@ hipError_t launch_all_to_all(const void* const* send, void* const* recv, int P, 
     const int64_t G = want < grid_limit(int64_t(1) << 20) ? (want > 0 ? want : 1) : grid_limit(int64_t(1) << 20);
     const int4* d = static_cast<const int4*>(desc);
     // XCD mode runs the per-XCD lists of the planner (each token row's copies on one XCD).
-    note_launch(vec ? "k_all_to_all" : "k_all_to_all_elem", mode == kPlaceXcd ? kMapXcdLists : kMapLinear, 0, G, kWG,
-                vec ? 4 : 0);
+    const int nt = vec ? pick_row_threads(rowlen) : kWG;
+    note_launch(vec ? "k_all_to_all" : "k_all_to_all_elem", mode == kPlaceXcd ? kMapXcdLists : kMapLinear, 0, G, nt,
+                vec ? kRowVpt : 0);
     if (vec) {
-        if (P <= 8) {
-            Ptrs<8> p = make_ptrs<8>(send, recv, P, P);
-            hipLaunchKernelGGL((k_all_to_all<8, 4>), dim3(static_cast<unsigned>(G)), dim3(kWG), 0, stream, p, P, d,
-                               rowlen, pl);
-        } else {
-            Ptrs<64> p = make_ptrs<64>(send, recv, P, P);
-            hipLaunchKernelGGL((k_all_to_all<64, 4>), dim3(static_cast<unsigned>(G)), dim3(kWG), 0, stream, p, P, d,
-                               rowlen, pl);
-        }
+        with_row_threads(nt, [&](auto n) { launch_a2a<n.value>(send, recv, P, d, rowlen, pl, G, stream); });
     } else {
         Ptrs<64> p = make_ptrs<64>(send, recv, P, P);
         if (esize == 4)

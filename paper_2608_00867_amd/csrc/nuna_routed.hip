@@ -26,10 +26,9 @@
 //                  tokens, up to 1024 per pass), 64 tokens per wave.  Each
 //                  lane forms its token's destination mask (its k entries
 //                  loaded together, as in k_route_small); a wave ballot per
-//                  destination d counts the wave's
-//                  tokens sent to d, and a scan of those counts over the waves
-//                  in LDS gives every token its rank among the tokens of s
-//                  sent to d.  Each token's record lists its destinations in
+//                  destination d counts the wave's tokens sent to d, and the
+//                  counts of the waves before it, summed from LDS, give every
+//                  token its rank among the tokens of s sent to d.  Each token's record lists its destinations in
 //                  ascending order as (rank within s << 6) | d, padded with
 //                  all ones; cnt[s][d] is the total.  (A first form, one wave
 //                  per source walking 64 tokens at a time, took 21 us at 512
@@ -38,9 +37,9 @@
 //                  j < R: it copies the token's row to the j-th destination of
 //                  its record (an empty slot does nothing).  The receive row of
 //                  copy d is sum over s' < s of cnt[s'][d] plus the rank within
-//                  s; up to 8 ranks every lane holds one cnt entry, loaded
-//                  beside the first record, and a wave sum adds the column
-//                  (beyond, the lanes q < s load cnt[q][d] together).  The R
+//                  s; up to 16 ranks the lanes hold cnt, loaded beside the
+//                  first record, and add the column (beyond, the lanes q < s
+//                  load cnt[q][d] together).  The R
 //                  items of a token read the same row: they are the logical
 //                  group of Sec. 4.2.1, and XCD placement runs them on
 //                  consecutive slots of one XCD (placement.h), so the row is
@@ -60,6 +59,7 @@
 // (k_route_small) uses no scratch.
 #include "device_common.h"
 #include "fastdiv.h"
+#include "shapes.h"
 
 namespace nuna {
 
@@ -75,7 +75,6 @@ constexpr int kRouteCountWaves = kRouteCountThreads / 64;
 constexpr int kRouteBatch = 8;            // top-k entries (or counts) loaded per round
 constexpr int kRouteSmallTokens = kWG;    // decode path: one token per thread
 constexpr int kRouteSmallEntries = 2048;  // decode path: top-k entries every workgroup reads
-constexpr int kRouteVpt = 4;              // 16-byte vectors per thread per column pass
 
 // Destination mask of one token: bit d set when one of its k experts lives on
 // rank d (expert e on rank e / per); entries outside [0, E) are counted in
@@ -140,20 +139,6 @@ __device__ __forceinline__ int64_t strided_sum(const int32_t* base, int stride, 
 __device__ __forceinline__ int wave_sum(int v) {
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
     return v;
-}
-
-// One token row to one destination row: the R items of a token read the same
-// row, so loads go through the caches; stores stream.
-__device__ __forceinline__ void copy_row(const uint4* src, uint4* dst, int64_t rowvec, int tid) {
-    for (int64_t v = tid; v < rowvec; v += int64_t(kWG) * kRouteVpt) {
-        uint4 y[kRouteVpt];
-#pragma unroll
-        for (int u = 0; u < kRouteVpt; ++u)
-            if (v + u * kWG < rowvec) y[u] = src[v + u * kWG];
-#pragma unroll
-        for (int u = 0; u < kRouteVpt; ++u)
-            if (v + u * kWG < rowvec) store_stream(dst + v + u * kWG, y[u]);
-    }
 }
 
 // Decode path: P*T <= kRouteSmallTokens tokens, one per thread.  Every
@@ -232,75 +217,127 @@ __global__ __launch_bounds__(kWG) void k_route_small(Ptrs<MAXP> p, const int32_t
         const int s = static_cast<int>(udiv(static_cast<uint32_t>(w), byT));
         const uint4* src = rank_in(tab, s) + static_cast<int64_t>(w - s * T) * rowvec;
         uint4* dst = rank_out(tab, d) + row * rowvec;
-        copy_row(src, dst, rowvec, tid);
+        copy_row<kWG, kRowVpt>(src, dst, rowvec, tid);
     }
 }
 
 // One workgroup per source rank s, of 64 threads per 64 tokens up to 1024
 // (a small launch keeps its scan and barriers short); each pass takes
 // blockDim.x tokens, wave w the 64 from t0 + 64 w.  Every lane loads its
-// token's k experts (one round of loads per pass), forms the token's
-// destination mask, and a wave ballot per destination d gives the token's
-// rank among the wave's tokens sent to d.
-// The waves' counts go through LDS, where an exclusive scan per destination
-// over the waves (and the passes before) gives each wave's offset; a second
-// ballot pass then writes the records.  The rank of a token is the number of
-// earlier tokens of s sent to d, whichever wave or pass counts them.
+// token's k experts (one round of loads per pass) and forms the token's
+// destination mask; a wave ballot per destination d gives the token's rank
+// among the wave's tokens sent to d.  The waves' counts go through LDS, where
+// every wave sums those of the waves before it: lane l takes destination
+// l mod MP of every (64 / MP)-th wave, and the lanes of a destination are added
+// by shuffles.  The rank of a token is the number of earlier tokens of s sent
+// to d, whichever wave or pass counts them.  MP: ranks rounded up to 8, 16, 64.
+//
+// The kernel is a chain of latencies on few waves: entries, LDS, records.  With
+// one thread per destination walking the waves' counts, three barriers a pass,
+// and the records stored word by word, the whole dispatch of 4 ranks, 100 tokens
+// of 7168 bf16 took 8.65 us, with this form 8.08.
+template <int MP>
 __global__ __launch_bounds__(kRouteCountThreads) void k_route_count(const int32_t* __restrict__ topk, int P, int T,
                                                                     int k, int E, int R, Magic per, int vec,
                                                                     unsigned char* scr) {
     int32_t* cnt = reinterpret_cast<int32_t*>(scr);
     int32_t* bad = cnt + P * P;
     uint32_t* rec = reinterpret_cast<uint32_t*>(bad + P);
-    __shared__ int wave_cnt[kRouteCountWaves][64];  // tokens of wave w sent to d (this pass)
-    __shared__ int offset[kRouteCountWaves][64];    // tokens of s sent to d before wave w's first token
-    __shared__ int carry[64];                       // tokens of s sent to d in earlier passes
+    __shared__ int wave_cnt[2][kRouteCountWaves][MP];  // tokens of wave w sent to d, by parity of the pass
     __shared__ int wave_bad[kRouteCountWaves];
     const int s = blockIdx.x;
     const int tid = threadIdx.x;
     const int wave = tid >> 6;
     const int lane = tid & 63;
-    const uint64_t below = (uint64_t(1) << lane) - 1;
-    if (tid < 64) carry[tid] = 0;
-    int nbad = 0;  // this lane's invalid entries
     const int nw = static_cast<int>(blockDim.x) >> 6;
-    for (int t0 = 0; t0 < T; t0 += static_cast<int>(blockDim.x)) {
+    int nbad = 0;   // this lane's invalid entries
+    int carry = 0;  // tokens of s sent to d = lane mod MP in earlier passes
+    int buf = 0;
+    for (int t0 = 0; t0 < T; t0 += static_cast<int>(blockDim.x), buf ^= 1) {
         const int t = t0 + tid;
         const uint64_t mask =
             t < T ? token_mask(topk + (static_cast<int64_t>(s) * T + t) * k, k, E, per, vec != 0, nbad) : 0;
         int mine = 0;  // lane d: tokens of this wave sent to d
-        for (int d = 0; d < P; ++d) {
-            const int c = __popcll(__ballot((mask >> d) & 1u));
-            if (lane == d) mine = c;
-        }
-        if (lane < P) wave_cnt[wave][lane] = mine;
-        __syncthreads();
-        if (tid < P) {
-            int run = carry[tid];
-            for (int w = 0; w < nw; ++w) {
-                offset[w][tid] = run;
-                run += wave_cnt[w][tid];
+        if constexpr (MP <= 16) {
+#pragma unroll
+            for (int d = 0; d < MP; ++d) {
+                const int c = __popcll(__ballot((mask >> d) & 1u));
+                if (lane == d) mine = c;
             }
-            carry[tid] = run;
+        } else {
+            for (int d = 0; d < P; ++d) {
+                const int c = __popcll(__ballot((mask >> d) & 1u));
+                if (lane == d) mine = c;
+            }
         }
+        if (lane < MP) wave_cnt[buf][wave][lane] = mine;
+        // One barrier a pass: the next pass writes the other buffer, and a wave writes this one again
+        // only after the barrier that every wave reaches having read it.
         __syncthreads();
-        if (t < T) {
-            uint32_t* my = rec + (static_cast<int64_t>(s) * T + t) * R;
+        int before = 0, all = 0;
+        constexpr int kStep = 64 / MP;
+#pragma unroll
+        for (int w0 = 0; w0 < kRouteCountWaves; w0 += kStep) {
+            const int w = w0 + lane / MP;
+            if (w0 < nw) {
+                const int c = w < nw ? wave_cnt[buf][w][lane & (MP - 1)] : 0;
+                before += w < wave ? c : 0;
+                all += c;
+            }
+        }
+        for (int off = MP; off < 64; off <<= 1) {
+            before += __shfl_xor(before, off);
+            all += __shfl_xor(all, off);
+        }
+        before += carry;
+        carry += all;
+        uint32_t* my = rec + (static_cast<int64_t>(s) * T + t) * R;
+        if constexpr (MP == 8) {
+            uint32_t word[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) word[j] = ~0u;
+            int j = 0;
+#pragma unroll
+            for (int d = 0; d < 8; ++d) {
+                const bool on = (mask >> d) & 1u;
+                const uint64_t bal = __ballot(on);
+                const uint32_t rank = __builtin_amdgcn_mbcnt_hi(
+                    static_cast<uint32_t>(bal >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(bal), 0u));
+                const uint32_t v =
+                    ((static_cast<uint32_t>(__builtin_amdgcn_readlane(before, d)) + rank) << 6) | static_cast<uint32_t>(d);
+#pragma unroll
+                for (int q = 0; q <= d; ++q) word[q] = on && j == q ? v : word[q];
+                j += on ? 1 : 0;
+            }
+            if (t < T) {
+                if ((R & 3) == 0 && (P * (P + 1) & 3) == 0) {  // records at multiples of 16 bytes
+                    uint4* out = reinterpret_cast<uint4*>(my);
+                    out[0] = make_uint4(word[0], word[1], word[2], word[3]);
+                    if (R == 8) out[1] = make_uint4(word[4], word[5], word[6], word[7]);
+                } else {
+#pragma unroll
+                    for (int q = 0; q < 8; ++q)
+                        if (q < R) my[q] = word[q];
+                }
+            }
+        } else {
+            // Lanes past T hold no token and are the wave's last: their bits are clear.
             int j = 0;
             for (int d = 0; d < P; ++d) {
                 const bool on = (mask >> d) & 1u;
                 const uint64_t bal = __ballot(on);
-                if (on) my[j++] = (static_cast<uint32_t>(offset[wave][d] + __popcll(bal & below)) << 6) |
-                                  static_cast<uint32_t>(d);
+                const uint32_t rank = __builtin_amdgcn_mbcnt_hi(
+                    static_cast<uint32_t>(bal >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(bal), 0u));
+                const uint32_t v =
+                    ((static_cast<uint32_t>(__builtin_amdgcn_readlane(before, d)) + rank) << 6) | static_cast<uint32_t>(d);
+                if (on) my[j++] = v;
             }
-            // Lanes past T hold no token and are the wave's last: left out of the ballots, they change
-            // no rank.
-            for (; j < R; ++j) my[j] = ~0u;
+            if (t < T)
+                for (; j < R; ++j) my[j] = ~0u;
         }
-        __syncthreads();  // offset and carry are rewritten by the next pass
     }
-    if (tid < P) cnt[s * P + tid] = carry[tid];
-    nbad = wave_sum(nbad);
+    if (wave == 0 && lane < P) cnt[s * P + lane] = carry;
+    if (__ballot(nbad != 0) != 0) nbad = wave_sum(nbad);  // rare: six dependent shuffles
     if (lane == 0) wave_bad[wave] = nbad;
     __syncthreads();
     if (tid == 0) {
@@ -310,44 +347,96 @@ __global__ __launch_bounds__(kRouteCountThreads) void k_route_count(const int32_
     }
 }
 
-template <int MAXP>
-__global__ __launch_bounds__(kWG) void k_route_copy(Ptrs<MAXP> p, int P, int T, int R, Magic byR, Magic byT,
-                                                    int64_t rowvec, int64_t cap, const unsigned char* scr,
-                                                    int64_t* rows_out, Place pl) {
+// First receive rows: those of destination d from source s start at the sum
+// over s' < s of cnt[s'][d].  Up to 16 ranks the lanes of every wave hold cnt
+// for the whole launch, loaded beside the first record: register q, lane l
+// that of source q * (64 / MP) + l / MP and destination l mod MP.
+template <int MP>
+struct RowBase {
+    static constexpr int kPer = 64 / MP, kRegs = MP / kPer;
+    int c[kRegs];
+
+    __device__ __forceinline__ void load(const int32_t* __restrict__ cnt, int P, int lane) {
+        const int d = lane & (MP - 1);
+#pragma unroll
+        for (int q = 0; q < kRegs; ++q) {
+            const int s = q * kPer + lane / MP;
+            c[q] = s < P && d < P ? cnt[s * P + d] : 0;
+        }
+    }
+    __device__ __forceinline__ int before(int s, int d, int lane) const {  // s, d uniform
+        int v = 0;
+#pragma unroll
+        for (int q = 0; q < kRegs; ++q) v += q * kPer + lane / MP < s ? c[q] : 0;
+        int sum = 0;
+#pragma unroll
+        for (int l = 0; l < 64; l += MP) sum += __builtin_amdgcn_readlane(v, l + d);
+        return sum;
+    }
+};
+
+// Bound by instructions and latency per item while rows are short: every
+// (token, slot) item is a workgroup of its own, so the item's address is
+// formed in 32-bit scalars (fewer than 2^21 records fit the scratch) and its
+// shape follows the row (pick_row_threads).
+template <int MAXP, int NT>
+__global__ __launch_bounds__(NT) void k_route_copy(Ptrs<MAXP> p, int P, int T, int R, int xcd, Magic byR, Magic byT,
+                                                   int64_t rowvec, int64_t cap, const int32_t* __restrict__ cnt,
+                                                   const int32_t* __restrict__ bad, const uint32_t* __restrict__ rec,
+                                                   int64_t* rows_out) {
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    constexpr int MP = MAXP <= 8 ? 8 : 16;
+    RowBase<MP> base;
+    if constexpr (MAXP <= 16) base.load(cnt, P, lane);
+    const RankTable tab = load_rank_table(p, P);
+    if (blockIdx.x == gridDim.x - 1) {
+        // Rows each rank receives (the caller compares them with its capacity)
+        // and the count of invalid top-k entries.
+        for (int r = tid; r <= P; r += NT) rows_out[r] = r < P ? strided_sum(cnt + r, P, P) : strided_sum(bad, 1, P);
+    }
+    // The uniform map of placement.h: workgroup b takes list positions i of its
+    // XCD x, position i being item i mod R of token x + 8 (i div R); with xcd = 0
+    // (the linear map) those of the whole list.
+    const uint32_t ntok = static_cast<uint32_t>(P) * static_cast<uint32_t>(T), uR = static_cast<uint32_t>(R);
+    const uint32_t x = xcd ? blockIdx.x & (kNumXcd - 1) : 0u;
+    const uint32_t end = xcd ? ((ntok + kNumXcd - 1 - x) >> 3) * uR : ntok * uR;
+    const uint32_t stride = xcd ? (gridDim.x - x + kNumXcd - 1) >> 3 : gridDim.x;
+    for (uint32_t i = xcd ? blockIdx.x >> 3 : blockIdx.x; i < end; i += stride) {
+        const uint32_t q = udiv(i, byR);
+        const uint32_t w = xcd ? x + kNumXcd * q : q;  // token (s, t)
+        const uint32_t word = rec[i + (w - q) * uR];
+        if (word == ~0u) continue;   // the token has fewer destinations than R
+        const int d = static_cast<int>(word & 63u);
+        const int s = static_cast<int>(udiv(w, byT));
+        int64_t row = static_cast<int64_t>(word >> 6);
+        if constexpr (MAXP <= 16)
+            row += base.before(s, d, lane);
+        else
+            row += wave_sum(lane < s ? cnt[lane * P + d] : 0);  // s < P <= 64
+        if (row >= cap) continue;    // beyond the caller's capacity: reported through rows_out
+        copy_row<NT, kRowVpt>(rank_in(tab, s) + (w - static_cast<uint32_t>(s) * static_cast<uint32_t>(T)) * rowvec,
+                          rank_out(tab, d) + row * rowvec, rowvec, tid);
+    }
+}
+
+template <int NT>
+void launch_route_copy(const void* const* send, void* const* recv, int P, int T, int R, int xcd, Magic byR, Magic byT,
+                       int64_t rowvec, int64_t cap, const unsigned char* scr, int64_t* rows_out, int64_t G,
+                       hipStream_t stream) {
     const int32_t* cnt = reinterpret_cast<const int32_t*>(scr);
     const int32_t* bad = cnt + P * P;
     const uint32_t* rec = reinterpret_cast<const uint32_t*>(bad + P);
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    // Up to 8 ranks, lane l holds cnt[l / P][l mod P] for the whole launch.
-    const bool lane_table = P * P <= 64;
-    const int held = lane_table && lane < P * P ? cnt[lane] : 0;
-    const int held_s = lane_table ? lane / P : 0;
-    const int held_d = lane_table ? lane - held_s * P : 0;
-    if (blockIdx.x == 0 && tid <= P) {
-        // Rows each rank receives (the caller compares them with its capacity)
-        // and the count of invalid top-k entries.
-        rows_out[tid] = tid < P ? strided_sum(cnt + tid, P, P) : strided_sum(bad, 1, P);
-    }
-    const RankTable tab = load_rank_table(p, P);
-    const ItemRange it = items_of(pl, blockIdx.x, gridDim.x);
-    for (int64_t i = it.first; i < it.end; i += it.stride) {
-        const int64_t item = item_at(pl, blockIdx.x, gridDim.x, i);  // < 2^21: the records fit the scratch
-        const uint32_t word = rec[item];
-        if (word == ~0u) continue;   // the token has fewer destinations than R
-        const int64_t w = udiv(static_cast<uint32_t>(item), byR);  // token (s, t) = w
-        const int d = static_cast<int>(word & 63u);
-        const int s = static_cast<int>(udiv(static_cast<uint32_t>(w), byT));
-        int part;
-        if (lane_table)
-            part = lane < P * P && held_d == d && held_s < s ? held : 0;
-        else
-            part = lane < s ? cnt[lane * P + d] : 0;  // s < P <= 64
-        const int64_t row = static_cast<int64_t>(word >> 6) + wave_sum(part);
-        if (row >= cap) continue;    // beyond the caller's capacity: reported through rows_out
-        copy_row(rank_in(tab, s) + (w - static_cast<int64_t>(s) * T) * rowvec, rank_out(tab, d) + row * rowvec, rowvec,
-                 tid);
-    }
+    const dim3 grid(static_cast<unsigned>(G)), block(NT);
+    if (P <= 8)
+        hipLaunchKernelGGL((k_route_copy<8, NT>), grid, block, 0, stream, make_ptrs<8>(send, recv, P, P), P, T, R,
+                           xcd, byR, byT, rowvec, cap, cnt, bad, rec, rows_out);
+    else if (P <= 16)
+        hipLaunchKernelGGL((k_route_copy<16, NT>), grid, block, 0, stream, make_ptrs<16>(send, recv, P, P), P, T,
+                           R, xcd, byR, byT, rowvec, cap, cnt, bad, rec, rows_out);
+    else
+        hipLaunchKernelGGL((k_route_copy<64, NT>), grid, block, 0, stream, make_ptrs<64>(send, recv, P, P), P, T,
+                           R, xcd, byR, byT, rowvec, cap, cnt, bad, rec, rows_out);
 }
 
 }  // namespace
@@ -371,7 +460,7 @@ hipError_t launch_routed_dispatch(const void* const* send, void* const* recv, co
     const Magic byT = make_magic(static_cast<uint32_t>(T > 0 ? T : 1));
     const int vec = (k % 4 == 0 && (reinterpret_cast<uintptr_t>(topk) & 15u) == 0) ? 1 : 0;
     if (ntok <= kRouteSmallTokens && ntok * k <= kRouteSmallEntries) {
-        note_launch("k_route_small", map, R, G, kWG, kRouteVpt);
+        note_launch("k_route_small", map, R, G, kWG, kRowVpt);
         if (P <= 8) {
             const Ptrs<8> p = make_ptrs<8>(send, recv, P, P);
             hipLaunchKernelGGL(k_route_small<8>, dim3(static_cast<unsigned>(G)), dim3(kWG), 0, stream, p, topk, P, T,
@@ -384,22 +473,22 @@ hipError_t launch_routed_dispatch(const void* const* send, void* const* recv, co
         return hipGetLastError();
     }
     unsigned char* scr = static_cast<unsigned char*>(scratch_ptr);
-    const int nt = T >= kRouteCountThreads ? kRouteCountThreads : (T < 64 ? 64 : (T + 63) / 64 * 64);
-    hipLaunchKernelGGL(k_route_count, dim3(static_cast<unsigned>(P)), dim3(static_cast<unsigned>(nt)), 0, stream, topk,
-                       P, T, k, E, R, per, vec, scr);
+    const int cnt_nt = T >= kRouteCountThreads ? kRouteCountThreads : (T < 64 ? 64 : (T + 63) / 64 * 64);
+    const int nt = pick_row_threads(rowvec);
+    const dim3 cg(static_cast<unsigned>(P)), cb(static_cast<unsigned>(cnt_nt));
+    if (P <= 8)
+        hipLaunchKernelGGL(k_route_count<8>, cg, cb, 0, stream, topk, P, T, k, E, R, per, vec, scr);
+    else if (P <= 16)
+        hipLaunchKernelGGL(k_route_count<16>, cg, cb, 0, stream, topk, P, T, k, E, R, per, vec, scr);
+    else
+        hipLaunchKernelGGL(k_route_count<64>, cg, cb, 0, stream, topk, P, T, k, E, R, per, vec, scr);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    note_launch("k_route_count+k_route_copy", map, R, G, kWG, kRouteVpt);
-    const unsigned char* cs = static_cast<const unsigned char*>(scratch_ptr);
-    if (P <= 8) {
-        const Ptrs<8> p = make_ptrs<8>(send, recv, P, P);
-        hipLaunchKernelGGL(k_route_copy<8>, dim3(static_cast<unsigned>(G)), dim3(kWG), 0, stream, p, P, T, R, byR,
-                           byT, rowvec, cap, cs, rows_out, pl);
-    } else {
-        const Ptrs<64> p = make_ptrs<64>(send, recv, P, P);
-        hipLaunchKernelGGL(k_route_copy<64>, dim3(static_cast<unsigned>(G)), dim3(kWG), 0, stream, p, P, T, R, byR,
-                           byT, rowvec, cap, cs, rows_out, pl);
-    }
+    note_launch("k_route_count+k_route_copy", map, R, G, nt, kRowVpt);
+    const int xcd = linear_map(pl, G) ? 0 : 1;
+    with_row_threads(nt, [&](auto n) {
+        launch_route_copy<n.value>(send, recv, P, T, R, xcd, byR, byT, rowvec, cap, scr, rows_out, G, stream);
+    });
     return hipGetLastError();
 }
 

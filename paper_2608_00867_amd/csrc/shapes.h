@@ -284,5 +284,28 @@ inline void pick_ar_shape(int64_t vectors_per_rank, int P, int dtype, int& nt, i
     }
 }
 
+// Threads of a row copy (rowvec 16-byte vectors, 4 per thread and pass).  One
+// workgroup copies one row, and with short rows the setup of its waves is what
+// the launch costs: as few waves as the row fills in one pass.  Dispatch of 8
+// ranks, 512 tokens, bf16, top-8, with 256 / 128 / 64 threads: 128 vectors
+// 16.7 / 12.7 / 8.9 us, 256 vectors 24.6 / 17.0 / 17.3, 360 vectors 25.2 / 23.4 /
+// 23.8, 512 vectors 31.8 / 32.5 / 34.8, 896 vectors 57.2 / 58.5 / 59.4.
+inline int pick_row_threads(int64_t rowvec) { return rowvec <= 256 ? 64 : rowvec < 512 ? 128 : kWG; }
+
+constexpr int kRowVpt = 4;
+
+template <int N>
+struct IntTag {
+    static constexpr int value = N;
+};
+
+// Calls f with the threads of a row copy as a compile-time constant.
+template <typename F>
+inline void with_row_threads(int nt, F&& f) {
+    if (nt == 64) f(IntTag<64>{});
+    else if (nt == 128) f(IntTag<128>{});
+    else f(IntTag<kWG>{});
+}
+
 }  // namespace
 }  // namespace nuna

@@ -5,6 +5,7 @@ import pytest
 
 import oracle
 from gpu_util import assert_bitwise, assert_bitwise_nan_aware, to_dev, to_host
+from test_zz_no_alloc import _check_case as check_routed
 from paper_2608_00867_amd import workloads as wl
 
 pytestmark = pytest.mark.gpu
@@ -196,3 +197,22 @@ def test_ragged_shards_under_a_workgroup_cap(nuna, cap):
     for d in range(P):
         assert_bitwise(got[d], ref[d], f"RS rank {d}")
         assert_bitwise(got_g[d], ref_g[d], f"AG rank {d}")
+
+
+@pytest.mark.parametrize("H", [8, 2048, 2056, 4088, 4096, 4104])
+@pytest.mark.parametrize("P,T,k,E", [(1, 260, 1, 1), (3, 87, 3, 12), (4, 130, 4, 32), (8, 33, 8, 64), (7, 150, 5, 28),
+                                     (9, 40, 4, 36), (16, 70, 8, 64), (17, 16, 8, 68)])
+def test_routed_row_lengths(nuna, P, T, k, E, H):
+    """The routed and the layout-driven dispatch at the row lengths where their threads change (256 and 512
+    vectors) and around them; rank counts at the edges of the counting kernel's 8, 16 and 64; records of 4, 8 and
+    odd words; the last wave of a source partly filled; a receive buffer with no row to spare."""
+    for place in ("linear", "xcd"):
+        check_routed(nuna, P, T, k, E, H, 31 * P + H, place, cap_extra=8 if place == "xcd" else 0)
+
+
+@pytest.mark.parametrize("grid", [5, 8, 61])
+def test_routed_row_lengths_under_a_workgroup_cap(nuna, grid):
+    with nuna.tunables(NUNA_MAX_GRID=grid):
+        for P, T, k, E, H in ((8, 40, 8, 64, 264), (12, 30, 3, 36, 2056), (33, 9, 2, 66, 4104)):
+            for place in ("linear", "xcd"):
+                check_routed(nuna, P, T, k, E, H, 77 + P, place)
