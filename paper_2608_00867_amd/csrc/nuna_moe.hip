@@ -18,7 +18,7 @@ namespace {
 // source token, destination rank, destination row.
 template <int MAXP, int NT>
 __global__ __launch_bounds__(NT) void k_all_to_all(Ptrs<MAXP> p, int P, const int4* __restrict__ desc,
-                                                    int64_t rowvec, Place pl) {
+                                                   int64_t rowvec, Place pl) {
     // The dispatch always runs per-XCD item lists (Place gsize 0).
     const RankTable tab = load_rank_table(p, P);
     // The scalar arguments the item loop needs go into one empty statement, so
@@ -296,8 +296,6 @@ void launch_combine_w(const void* const* y, void* const* out, int P, const int64
     else launch_combine_t<MAXP, DT, false>(y, out, P, off, ent, rec, w, s, items, G, nt, vpt, st);
 }
 
-}  // namespace
-
 template <int NT>
 void launch_a2a(const void* const* send, void* const* recv, int P, const int4* d, int64_t rowvec, const Place& pl,
                 int64_t G, hipStream_t stream) {
@@ -309,6 +307,8 @@ void launch_a2a(const void* const* send, void* const* recv, int P, const int4* d
         hipLaunchKernelGGL((k_all_to_all<64, NT>), grid, block, 0, stream, make_ptrs<64>(send, recv, P, P), P, d,
                            rowvec, pl);
 }
+
+}  // namespace
 
 hipError_t launch_all_to_all(const void* const* send, void* const* recv, int P, const void* desc, int64_t nitems,
                              const int64_t* xcd_start, size_t row_bytes, int esize, int mode, hipStream_t stream) {
@@ -367,16 +367,21 @@ hipError_t launch_combine(const void* const* y, void* const* out, int P, int T, 
         s.P = P;
         const int forced = tuning().wg_threads;
         const int nt = forced == 64 || forced == 128 || forced == 256 ? forced : 256;
-        // Default vectors per thread: 1 with the records (measured on MI355X at
-        // 16, 128 and 512 tokens per rank, 8 ranks, 7168-wide rows: equal or
-        // faster, up to 11 % at 16 tokens), 2 with the offset lists.
+        // Default vectors per thread: 1.  With the records, measured on MI355X at
+        // 16, 128 and 512 tokens per rank, 8 ranks, 7168-wide rows: equal to 2 or
+        // faster, up to 11 % at 16 tokens.  With the lists, 16 ranks, bf16, and
+        // chunks of one pass below, against 2 vectors in several passes: 200
+        // tokens x 4096, top-2, 20.2 -> 14.7 us, 128 x 2048, top-8, 14.1 -> 12.2,
+        // 4 x 7168 4.1 -> 3.5, 128 x 7168 38.1 -> 37.7.
         const int fv = tuning().combine_vpt;
-        const int vpt = fv == 1 || fv == 2 || fv == 4 ? fv : rc ? 1 : 2;
+        const int vpt = fv == 1 || fv == 2 || fv == 4 ? fv : 1;
         s.chunks = pick_combine_chunks(ntok, s.rowvec, nt);
         s.cw = (s.rowvec + s.chunks - 1) / s.chunks;
-        if (rc && s.cw > static_cast<int64_t>(nt) * vpt) {
+        if (s.cw > static_cast<int64_t>(nt) * vpt && (rc || tuning().combine_chunks == 0)) {
             // The record kernel covers a chunk in one pass: at most nt * vpt
-            // vectors per chunk.  Work items are numbered in 32 bits.
+            // vectors per chunk.  The list kernel loops over any chunk, but does
+            // best with one pass as well (figures above); a chunk count that the
+            // caller fixes stays.  Work items are numbered in 32 bits.
             const int64_t need = (s.rowvec + static_cast<int64_t>(nt) * vpt - 1) / (static_cast<int64_t>(nt) * vpt);
             if (ntok * need <= int64_t(UINT32_MAX)) {
                 s.chunks = static_cast<uint32_t>(need);

@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 
 import oracle
-from gpu_util import assert_bitwise, assert_bitwise_nan_aware, to_dev, to_host
+from gpu_util import assert_bitwise, assert_bitwise_nan_aware, run_combine, to_dev, to_host
 from test_zz_no_alloc import _check_case as check_routed
 from paper_2608_00867_amd import workloads as wl
 
@@ -216,3 +216,26 @@ def test_routed_row_lengths_under_a_workgroup_cap(nuna, grid):
         for P, T, k, E, H in ((8, 40, 8, 64, 264), (12, 30, 3, 36, 2056), (33, 9, 2, 66, 4104)):
             for place in ("linear", "xcd"):
                 check_routed(nuna, P, T, k, E, H, 77 + P, place)
+
+
+@pytest.mark.parametrize("dtype", [np.uint16, np.float32])
+@pytest.mark.parametrize("P,T,k,E", [(9, 5, 4, 36), (16, 3, 8, 64), (33, 4, 8, 66), (8, 6, 8, 64)])
+def test_combine_lists_row_lengths(nuna, P, T, k, E, dtype):
+    """The combine from offset lists, one pass per column chunk: rows of one vector, of a workgroup's 256 and one
+    more or less, of several chunks with a short last one; plain and weighted; a fixed chunk count of several
+    passes.  8 ranks: the lists by the tunable."""
+    topk = wl.moe_routing(P, T, k, E, 5 * P)
+    lanes = 8 if dtype == np.uint16 else 4
+    lay = nuna.A2ALayout(topk, E)
+    rows = [int(r) for r in lay.recv_rows()]
+    lay.close()
+    weights = wl.gate_weights(topk, E, 9)
+    for vecs, tune in ((1, {}), (255, {}), (256, {}), (257, {}), (700, {}), (1025, {}), (700, {"NUNA_COMBINE_CHUNKS": 1})):
+        H = vecs * lanes
+        y = wl.result_rows(rows, H, dtype, vecs)
+        for w in (None, weights):
+            want = oracle.combine(y, topk, E, w)
+            with nuna.tunables(**dict(tune, NUNA_COMBINE_LISTS=1)):
+                got = run_combine(nuna, y, topk, E, "xcd", weights=w)
+            for s in range(P):
+                assert_bitwise(got[s], want[s], f"combine lists P={P} vecs={vecs} {tune} w={w is not None} rank {s}")
