@@ -19,6 +19,8 @@
 #include <string>
 #include <vector>
 
+#include "a2a_order.h"
+#include "fastdiv.h"
 #include "kernels.h"
 #include "nap_planner.h"
 #include "nuna.h"
@@ -597,6 +599,7 @@ nuna_status_t nuna_a2a_layout_create(int P, int tokens_per_rank, int topk, int n
             return fail(NUNA_ERR_INVALID_ARG, "topk_idx[%lld]=%d outside [0, %d)", static_cast<long long>(i),
                         topk_idx[i], num_experts);
 
+    const nuna::Magic by_per = nuna::make_magic(static_cast<uint32_t>(per));
     std::unique_ptr<nuna_a2a_layout> L(new nuna_a2a_layout());
     L->P = P;
     L->T = tokens_per_rank;
@@ -607,10 +610,10 @@ nuna_status_t nuna_a2a_layout_create(int P, int tokens_per_rank, int topk, int n
     std::vector<uint64_t> mask(static_cast<size_t>(ntok));
     for (int64_t i = 0; i < ntok; ++i) {
         uint64_t m = 0;
-        for (int j = 0; j < topk; ++j) m |= uint64_t(1) << (topk_idx[i * topk + j] / per);
+        for (int j = 0; j < topk; ++j)
+            m |= uint64_t(1) << nuna::udiv(static_cast<uint32_t>(topk_idx[i * topk + j]), by_per);
         mask[i] = m;
-        for (int d = 0; d < P; ++d)
-            if (m >> d & 1u) ++L->rows[d];
+        for (uint64_t rest = m; rest; rest &= rest - 1) ++L->rows[__builtin_ctzll(rest)];
     }
     L->dst_off.assign(P + 1, 0);
     for (int d = 0; d < P; ++d) L->dst_off[d + 1] = L->dst_off[d] + L->rows[d];
@@ -624,72 +627,54 @@ nuna_status_t nuna_a2a_layout_create(int P, int tokens_per_rank, int topk, int n
     // destinations ascending.
     std::vector<int64_t> next(P, 0);
     L->comb_off.assign(static_cast<size_t>(ntok) + 1, 0);
-    L->comb_ent.reserve(2 * L->nitems);
+    L->comb_ent.resize(2 * L->nitems);
     // Row indices stay below ntok < 2^29, so no entry is all ones.
     const bool records = P <= nuna::kCombRecRanks && ntok < (int64_t(1) << 29);
     if (records) L->comb_rec.assign(static_cast<size_t>(ntok) * nuna::kCombRecRanks, ~uint32_t(0));
-    // Placement workload for the XCD mode: one threadblock per row copy, in
-    // walk order, touching its source row and its destination row.
-    std::vector<int64_t> tb_off(static_cast<size_t>(L->nitems) + 1, 0);
-    std::vector<int64_t> tb_chunk(2 * static_cast<size_t>(L->nitems));
-    std::vector<int32_t> walk_desc(4 * static_cast<size_t>(L->nitems));
-    int64_t w = 0;
+    // XCD of every token's copies (Algorithm 1, a2a_order.h), and from the
+    // copies per XCD where its list starts.  The algorithm fixes where a group
+    // runs, not when: each XCD runs its groups in token order, which keeps its
+    // source-row reads in address order (dealing them in size order measured
+    // 4 % slower on MI355X).
+    std::vector<uint8_t> xcd(static_cast<size_t>(ntok));
+    int64_t xcd_copies[NUNA_NUM_XCD];
+    nuna::a2a_token_xcds(mask.data(), ntok, xcd.data(), xcd_copies);
+    int64_t xcd_next[NUNA_NUM_XCD];  // each XCD's next position in desc_group
+    for (int x = 0; x < NUNA_NUM_XCD; ++x) {
+        xcd_next[x] = L->xcd_start[x];
+        L->xcd_start[x + 1] = L->xcd_start[x] + xcd_copies[x];
+    }
+    L->desc_group.resize(4 * L->nitems);
+    int64_t e = 0;  // the token's next combine entry
     for (int s = 0; s < P; ++s) {
         for (int t = 0; t < tokens_per_rank; ++t) {
             const size_t tok = static_cast<size_t>(s) * tokens_per_rank + t;
             const uint64_t m = mask[tok];
-            L->comb_off[tok + 1] = L->comb_off[tok] + __builtin_popcountll(m);
+            int64_t& at = xcd_next[xcd[tok]];
             size_t q_rec = tok * nuna::kCombRecRanks;  // the token's next record word
-            for (int d = 0; d < P; ++d) {
-                if (!(m >> d & 1u)) continue;
+            for (uint64_t rest = m; rest; rest &= rest - 1, ++e) {
+                const int d = __builtin_ctzll(rest);
                 const int64_t j = next[d]++;
                 const int64_t pos = L->dst_off[d] + j;
                 L->map_src[pos] = s;
                 L->map_tok[pos] = t;
                 const int32_t q[4] = {s, t, d, static_cast<int32_t>(j)};
                 std::memcpy(&L->desc_linear[4 * pos], q, sizeof q);
-                std::memcpy(&walk_desc[4 * static_cast<size_t>(w)], q, sizeof q);
-                tb_chunk[2 * static_cast<size_t>(w)] = static_cast<int64_t>(tok);        // source row
-                tb_chunk[2 * static_cast<size_t>(w) + 1] = ntok + pos;                    // destination row
-                tb_off[static_cast<size_t>(w) + 1] = 2 * (w + 1);
-                ++w;
+                std::memcpy(&L->desc_group[4 * at++], q, sizeof q);
                 if (records) L->comb_rec[q_rec++] = static_cast<uint32_t>(j) << 3 | static_cast<uint32_t>(d);
-                L->comb_ent.push_back(d);
-                L->comb_ent.push_back(static_cast<int32_t>(j));
+                L->comb_ent[2 * e] = d;
+                L->comb_ent[2 * e + 1] = static_cast<int32_t>(j);
             }
+            L->comb_off[tok + 1] = e;
         }
     }
-    // XCD assignment from the placement planner (Algorithm 1): the copies of
-    // one token share its source row and form one logical group; groups go to
-    // the 8 XCDs round-robin in decreasing size order, which evens out the
-    // copies per XCD.  Every copy is charged the same, so the budgets never
-    // bind and only the domain choice matters.  The algorithm fixes where a
-    // group runs, not when: each XCD runs its groups in token order, which
-    // keeps its source-row reads in address order (dealing them in size order
-    // measured 4 % slower on MI355X).
-    const std::vector<int64_t> unit(static_cast<size_t>(L->nitems), 1);
-    const nuna::NapPlan plan = nuna::nap_plan(nuna::nap_topology_mi355x(), NUNA_NUM_XCD, L->nitems, tb_off.data(),
-                                              tb_chunk.data(), unit.data(), nullptr);
-    std::vector<std::vector<int32_t>> per_xcd(NUNA_NUM_XCD);
-    for (size_t g = 0; g < plan.groups.size(); ++g) {
-        const std::vector<int64_t>& members = plan.groups[g];
-        std::vector<int32_t>& lst = per_xcd[static_cast<size_t>(plan.tb_domain[static_cast<size_t>(members[0])])];
-        for (int64_t tb : members)
-            lst.insert(lst.end(), &walk_desc[4 * static_cast<size_t>(tb)], &walk_desc[4 * static_cast<size_t>(tb)] + 4);
-    }
-    L->desc_group.reserve(4 * L->nitems);
-    for (int x = 0; x < NUNA_NUM_XCD; ++x) {
-        L->xcd_start[x] = static_cast<int64_t>(L->desc_group.size() / 4);
-        L->desc_group.insert(L->desc_group.end(), per_xcd[x].begin(), per_xcd[x].end());
-    }
-    L->xcd_start[NUNA_NUM_XCD] = L->nitems;
     *out = L.release();
     return ok();
 } catch (...) {
     return host_exception();
 }
 
-nuna_status_t nuna_a2a_layout_upload(nuna_a2a_layout_t* L) {
+nuna_status_t nuna_a2a_layout_upload(nuna_a2a_layout_t* L) try {
     if (!L) return fail(NUNA_ERR_INVALID_ARG, "layout is NULL");
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -711,9 +696,6 @@ nuna_status_t nuna_a2a_layout_upload(nuna_a2a_layout_t* L) {
     const size_t at_rec = (2 * n_desc + n_off + n_ent + 31) & ~size_t(31);
     const size_t n_rec = L->comb_rec.size() * sizeof(uint32_t);
     const size_t bytes = at_rec + n_rec;
-    void* base = nullptr;
-    if ((e = hipMalloc(&base, bytes)) != hipSuccess) return hip_status(e, "hipMalloc (a2a tables)");
-    char* b = static_cast<char*>(base);
     const struct {
         size_t at;
         const void* src;
@@ -723,12 +705,28 @@ nuna_status_t nuna_a2a_layout_upload(nuna_a2a_layout_t* L) {
                   {2 * n_desc, L->comb_off.data(), L->comb_off.size() * sizeof(int64_t)},
                   {2 * n_desc + n_off, L->comb_ent.data(), L->comb_ent.size() * sizeof(int32_t)},
                   {at_rec, L->comb_rec.data(), n_rec}};
-    for (const auto& q : parts) {
-        if (q.n == 0) continue;
-        if ((e = hipMemcpy(b + q.at, q.src, q.n, hipMemcpyHostToDevice)) != hipSuccess) {
-            (void)hipFree(base);
-            return hip_status(e, "hipMemcpy (a2a tables)");
+    // Laid out on the host first, the tables go up in one copy: 22 us against 70
+    // with a copy per table at 8 ranks, 128 tokens.  A large layout, where the
+    // bytes count and not the calls, needs no second host copy.
+    constexpr size_t kStagedBytes = size_t(16) << 20;
+    std::vector<char> host(bytes <= kStagedBytes ? bytes : 0);
+    if (!host.empty())
+        for (const auto& q : parts)
+            if (q.n) std::memcpy(host.data() + q.at, q.src, q.n);
+    void* base = nullptr;
+    if ((e = hipMalloc(&base, bytes)) != hipSuccess) return hip_status(e, "hipMalloc (a2a tables)");
+    char* b = static_cast<char*>(base);
+    if (!host.empty()) {
+        e = hipMemcpy(b, host.data(), bytes, hipMemcpyHostToDevice);
+    } else {
+        for (const auto& q : parts) {
+            if (q.n == 0) continue;
+            if ((e = hipMemcpy(b + q.at, q.src, q.n, hipMemcpyHostToDevice)) != hipSuccess) break;
         }
+    }
+    if (e != hipSuccess) {
+        (void)hipFree(base);
+        return hip_status(e, "hipMemcpy (a2a tables)");
     }
     L->dev_base = base;
     L->dev_linear = b;
@@ -738,6 +736,8 @@ nuna_status_t nuna_a2a_layout_upload(nuna_a2a_layout_t* L) {
     L->dev_comb_rec = n_rec ? b + at_rec : nullptr;
     L->device = dev;
     return ok();
+} catch (...) {
+    return host_exception();
 }
 
 nuna_status_t nuna_a2a_layout_recv_rows(const nuna_a2a_layout_t* L, int64_t* rows_per_rank) {
