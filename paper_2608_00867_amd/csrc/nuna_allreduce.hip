@@ -167,7 +167,7 @@ __global__ __launch_bounds__(kWG) void k_allreduce_direct(Ptrs<rank_cap<PT>()> p
     const RankTable tab{0u, 0u, 0u, 0u};  // pointers come from the arguments
     if ((c + 1) * cv <= nvec)
         allreduce_chunk<PT, DT, VPT, true, true, WT>(p, tab, s, P, v0, nt, 0, true, c * cv);
-    else
+    else if (PT > 0 || nvec > 0)  // a message of less than a vector has a tail only
         allreduce_chunk<PT, DT, VPT, false, true, WT>(p, tab, s, P, v0, nt, 0, true, c * cv);
     if (tail > 0 && blockIdx.x == 0) tail_elements<PT, DT>(p, tab, P, nvec, tail);
 }

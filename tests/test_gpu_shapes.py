@@ -1,0 +1,110 @@
+"""GPU: the launch shapes that a workgroup cap, the split and the two-shot all-reduce and the rank-count rules
+choose, by the launch record, with results against the oracle bit for bit; and two chunk forms whose loads have
+to be in flight together, by their time beside that of whole chunks."""
+import numpy as np
+import pytest
+
+import oracle
+from gpu_util import assert_bitwise, to_dev, to_host
+from test_gpu_parity import run_allreduce
+from paper_2608_00867_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+MIB = 1 << 20
+ES = {"bf16": 2, "f32": 4}
+
+
+@pytest.fixture(scope="module")
+def nuna():
+    from paper_2608_00867_amd import nuna as n
+    n.init()
+    return n
+
+
+@pytest.fixture(autouse=True)
+def _free():
+    yield
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+
+
+def _values(P, n, dtype, seed):
+    return wl.normal_bf16(P, n, seed) if dtype == "bf16" else wl.normal_f32(P, n, seed)
+
+
+def _allreduce(nuna, P, dtype, n, what, algo="one_shot", check=True):
+    """The launch record of one all-reduce of n elements per rank, checked on three ranks."""
+    x = _values(P, n, dtype, 7 * P + n % 101) if check else None
+    if check:
+        ins = [to_dev(a) for a in x]
+    else:
+        ins = [torch.zeros(n, dtype=torch.bfloat16 if dtype == "bf16" else torch.float32, device="cuda")
+               for _ in range(P)]
+    outs = nuna.allreduce(ins, algo=algo)
+    rec = nuna.last_launch()
+    torch.cuda.synchronize()
+    if check:
+        ref = oracle.allreduce(x)
+        for d in {0, P // 2, P - 1}:
+            assert_bitwise(to_host(outs[d]), ref[d], f"{what} rank {d}")
+    return rec
+
+
+def _us(call, n=60):
+    """Device time of one call, from the fastest of several replays of a graph of n."""
+    call()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        for _ in range(n):
+            call()
+    best = []
+    for _ in range(9):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        g.replay()
+        b.record()
+        torch.cuda.synchronize()
+        best.append(a.elapsed_time(b) * 1e3 / n)
+    return min(best)
+
+
+# ---------------------------------------------------------------- loads in flight together
+
+@pytest.mark.parametrize("P,chunks", [(6, 220), (9, 200), (12, 190), (14, 202), (15, 108)])
+def test_a_partial_chunk_takes_no_longer_than_a_whole_one(nuna, P, chunks):
+    """Run-time rank counts, bf16, 256 threads with one vector: a message that ends in a partial chunk runs in
+    the time of one that does not.  With its ranks loaded one after another the last workgroup alone took as long
+    again as the whole launch (1.3-2.0 times the time of whole chunks); loaded together, within 6 %."""
+    def time(n):
+        ins = [torch.zeros(n, dtype=torch.bfloat16, device="cuda") for _ in range(P)]
+        outs = [torch.empty_like(t) for t in ins]
+        call = nuna.prepare_allreduce(ins, outs)
+        call()
+        assert nuna.last_launch()["threads"] == 256 and nuna.last_launch()["kernels"] == "k_allreduce_direct"
+        return _us(lambda: call(torch.cuda.current_stream().cuda_stream))
+
+    whole, partial = time(chunks * 2048), time(chunks * 2048 - 1024)
+    assert partial < 1.2 * whole, (partial, whole)
+
+
+@pytest.mark.parametrize("P", [3, 7, 13])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_messages_below_a_vector_and_partial_chunks(nuna, P, dtype):
+    """Run-time rank counts: less than one vector (a tail alone), one vector, and partial chunks whose lanes past
+    the end load the last vector; in place, guard bands by the caller's neighbours."""
+    lanes = 16 // ES[dtype]
+    for n in (1, lanes - 1, lanes, lanes + 1, 255 * lanes, 257 * lanes + 1, 70001):
+        x = _values(P, n, dtype, 3 * P + n)
+        ref = oracle.allreduce(x)
+        with nuna.tunables(NUNA_LPR_MIN_RANKS=65):
+            got = run_allreduce(nuna, x, "one_shot", "xcd")
+            bufs = [to_dev(a) for a in x]
+            nuna.allreduce(bufs, bufs, algo="one_shot")
+            torch.cuda.synchronize()
+        for d in range(P):
+            assert_bitwise(got[d], ref[d], f"P={P} {dtype} n={n} rank {d}")
+            assert_bitwise(to_host(bufs[d]), ref[d], f"P={P} {dtype} n={n} in place rank {d}")
