@@ -108,3 +108,11 @@ def test_messages_below_a_vector_and_partial_chunks(nuna, P, dtype):
         for d in range(P):
             assert_bitwise(got[d], ref[d], f"P={P} {dtype} n={n} rank {d}")
             assert_bitwise(to_host(bufs[d]), ref[d], f"P={P} {dtype} n={n} in place rank {d}")
+
+
+@pytest.mark.parametrize("P", [17, 24, 33, 64])
+def test_tails_of_many_ranks(nuna, P):
+    """Elements after the last vector, summed 16 ranks at a time: one round and a rest, and four whole rounds."""
+    for dtype in ("bf16", "f32"):
+        for n in (3, 16 * (16 // ES[dtype]) + 1, 5003):
+            _allreduce(nuna, P, dtype, n, f"tail P={P} {dtype} n={n}")
