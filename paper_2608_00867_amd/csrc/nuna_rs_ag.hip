@@ -163,6 +163,9 @@ __device__ __forceinline__ void reduce_ranks_any(const Ptrs<MAXP>& p, const Rank
                     buf[q][j] = load16_any<false>(src + v * 16);
                 }
             }
+        // Loads first: the scheduler otherwise runs the ranks of a partial chunk one after another
+        // (16 ranks of bf16, 8191 elements per shard, 4.58 us against 3.4).
+        if constexpr (PT == 16 && DT == kDtBf16 && VPT == 1 && !FULL) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int q = 0; q < B; ++q)
             if (PT > 0 || r0 + q < P) {
