@@ -719,7 +719,11 @@ hipError_t launch_allreduce(const void* const* in, void* const* out, int P, size
         if (static_cast<int64_t>(bytes / 16) * P <= tuning().lpr_max_vectors)
             return launch_allreduce_lpr(in, out, P, count, dtype, mode, stream);
         int tv = tuning().tile_v;
-        if (tv == 0 && bytes <= (size_t(256) << 10)) tv = 16;
+        // Below 16 ranks not under a workgroup cap: its items of 16 vectors make too many
+        // rounds (12 ranks at 256 KiB, cap 64: 16.6 us, the general kernel 3.7).
+        if (tv == 0 && bytes <= (size_t(256) << 10) &&
+            (P >= 16 || !grid_capped((static_cast<int64_t>(bytes / 16) + 15) / 16)))
+            tv = 16;
         if (tv == 16 || tv == 32 || tv == 64) return launch_allreduce_tile(in, out, P, count, dtype, tv, mode, stream);
     }
     ArShape s{};
@@ -731,6 +735,15 @@ hipError_t launch_allreduce(const void* const* in, void* const* out, int P, size
     s.dpi = P / gsize;
     int nt, vpt;
     pick_ar_shape(s.nvec, P, dtype, nt, vpt);
+    if (grid_capped((s.nvec + static_cast<int64_t>(nt) * vpt - 1) / (static_cast<int64_t>(nt) * vpt) * gsize)) {
+        shared_ar_shape(s.nvec, P, nt, vpt);
+        if (gsize == 1 && dtype == kDtBf16 && nt == 128 && vpt == 4 && !tuning().wg_threads && !tuning().vpt) {
+            // The same vectors in flight on twice the waves, which the loop of the general kernel
+            // needs for bf16 (cap 64, 8 ranks, 4 MiB: 38.4 us with 128x4, 28.3 with 256x2; 6 MiB 59 and 44).
+            nt = 256;
+            vpt = 2;
+        }
+    }
     if (vpt == 8 && P != 2 && P != 4 && P != 8) return hipErrorInvalidValue;
     const int64_t cv = static_cast<int64_t>(nt) * vpt;
     const int64_t groups = (s.nvec + cv - 1) / cv;
@@ -823,6 +836,8 @@ hipError_t launch_two_shot_fused(const void* const* in, void* const* out, int P,
     const int64_t mv = nvec / P;
     int nt, vpt;
     pick_ar_shape(nvec, P, dtype, nt, vpt);
+    const int64_t row_cv = static_cast<int64_t>(nt) * vpt;
+    if (grid_capped((mv + row_cv - 1) / row_cv * P)) shared_ar_shape(nvec, P, nt, vpt);
     if (vpt == 8 && P == 16) vpt = 4;
     const int64_t cv = static_cast<int64_t>(nt) * vpt;
     const int64_t wcs = (mv + cv - 1) / cv;

@@ -335,7 +335,7 @@ hipError_t launch_all_to_all(const void* const* send, void* const* recv, int P, 
     const int64_t G = want < grid_limit(int64_t(1) << 20) ? (want > 0 ? want : 1) : grid_limit(int64_t(1) << 20);
     const int4* d = static_cast<const int4*>(desc);
     // XCD mode runs the per-XCD lists of the planner (each token row's copies on one XCD).
-    const int nt = vec ? pick_row_threads(rowlen) : kWG;
+    const int nt = vec ? pick_row_threads(rowlen, grid_capped(want)) : kWG;
     note_launch(vec ? "k_all_to_all" : "k_all_to_all_elem", mode == kPlaceXcd ? kMapXcdLists : kMapLinear, 0, G, nt,
                 vec ? kRowVpt : 0);
     if (vec) {
@@ -373,11 +373,14 @@ hipError_t launch_combine(const void* const* y, void* const* out, int P, int T, 
         // chunks of one pass below, against 2 vectors in several passes: 200
         // tokens x 4096, top-2, 20.2 -> 14.7 us, 128 x 2048, top-8, 14.1 -> 12.2,
         // 4 x 7168 4.1 -> 3.5, 128 x 7168 38.1 -> 37.7.
+        // Under a caller's workgroup cap the lists keep 2 vectors and several
+        // passes: cap 64, 16 ranks, 60 tokens x 2880, 38.1 us against 54.6.
         const int fv = tuning().combine_vpt;
-        const int vpt = fv == 1 || fv == 2 || fv == 4 ? fv : 1;
+        const bool capped = !rc && grid_capped(ntok * ((s.rowvec + nt - 1) / nt));
+        const int vpt = fv == 1 || fv == 2 || fv == 4 ? fv : capped ? 2 : 1;
         s.chunks = pick_combine_chunks(ntok, s.rowvec, nt);
         s.cw = (s.rowvec + s.chunks - 1) / s.chunks;
-        if (s.cw > static_cast<int64_t>(nt) * vpt && (rc || tuning().combine_chunks == 0)) {
+        if (s.cw > static_cast<int64_t>(nt) * vpt && (rc || (tuning().combine_chunks == 0 && !capped))) {
             // The record kernel covers a chunk in one pass: at most nt * vpt
             // vectors per chunk.  The list kernel loops over any chunk, but does
             // best with one pass as well (figures above); a chunk count that the

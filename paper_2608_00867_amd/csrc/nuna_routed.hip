@@ -474,7 +474,7 @@ hipError_t launch_routed_dispatch(const void* const* send, void* const* recv, co
     }
     unsigned char* scr = static_cast<unsigned char*>(scratch_ptr);
     const int cnt_nt = T >= kRouteCountThreads ? kRouteCountThreads : (T < 64 ? 64 : (T + 63) / 64 * 64);
-    const int nt = pick_row_threads(rowvec);
+    const int nt = pick_row_threads(rowvec, grid_capped(want));
     const dim3 cg(static_cast<unsigned>(P)), cb(static_cast<unsigned>(cnt_nt));
     if (P <= 8)
         hipLaunchKernelGGL(k_route_count<8>, cg, cb, 0, stream, topk, P, T, k, E, R, per, vec, scr);

@@ -647,6 +647,10 @@ hipError_t launch_reduce_scatter(const void* const* in, void* const* out, int P,
     // Shape by the vectors each input rank holds (P shards of mv vectors).
     int nt, vpt;
     pick_rs_shape(s.mv * P, P, dtype, nt, vpt);
+    const int64_t row_cv = static_cast<int64_t>(nt) * vpt;
+    if (grid_capped((s.mv + row_cv - 1) / row_cv * P)) {
+        pick_rs_capped_shape(s.mv * P, P, dtype, nt, vpt);
+    }
     const int64_t cv = static_cast<int64_t>(nt) * vpt;
     s.wcs = (s.mv + cv - 1) / cv;
     const Place pl = make_place_uniform(mode, s.wcs * P, 1);

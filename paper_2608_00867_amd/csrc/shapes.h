@@ -123,6 +123,16 @@ inline int pick_threads(int64_t vectors_per_rank, int P) {
     return kWG;
 }
 
+// Whether a workgroup cap that the caller set (nuna_set_max_workgroups,
+// NUNA_MAX_GRID) keeps a launch of `items` work items from running one
+// workgroup each.  The workgroups then walk over the items, few of them, and
+// what each has in flight decides, not how many small ones fill the chip: the
+// rows of small workgroups below are for launches that the cap leaves alone.
+// Under a cap of 64, 8 ranks of bf16 reduce-scattered 192 KiB shards in 9.9 us
+// with 256 threads and 27 with the 64 of the row, and 6 ranks all-reduced
+// 1.5 MiB in 12.4 against 36.
+inline bool grid_capped(int64_t items) { return items > grid_limit(INT64_MAX); }
+
 // Launch shapes by size: rows in quarter MiB (per rank, as the rule using them
 // says), each row holding from its size on; nt 0 leaves the shape as it was.
 struct ShapeRow {
@@ -175,6 +185,21 @@ inline void pick_rs_shape(int64_t in_vectors, int P, int dtype, int& nt, int& vp
     else row_shape(k16, in_vectors, nt, vpt);
 }
 
+// Reduce-scatter under a workgroup cap: 256 threads, fp32 with 1 vector per
+// thread, bf16 with 4 from 8 MiB of input per rank and 128 x 2 at 4 MiB.
+inline void pick_rs_capped_shape(int64_t in_vectors, int P, int dtype, int& nt, int& vpt) {
+    nt = pick_threads(in_vectors, P);
+    vpt = dtype == kDtBf16 || tuning().vpt ? pick_vpt(in_vectors, P) : 1;
+    if (P > 16 || dtype != kDtBf16 || tuning().wg_threads || tuning().vpt) return;
+    if (in_vectors >= (int64_t(1) << 19)) {
+        nt = 256;
+        vpt = 4;
+    } else if (in_vectors >= (int64_t(1) << 18)) {
+        nt = 128;
+        vpt = 2;
+    }
+}
+
 // All-gather launch shape by the vectors each output rank receives, for up
 // to 16 ranks (measured on MI355X with bf16, 8 ranks, cold): one-wave
 // workgroups with 1 vector per thread below 2 MiB per output, 64 threads with
@@ -210,12 +235,38 @@ inline void pick_ag_shape(int64_t out_vectors, int P, int& nt, int& vpt) {
     }
 }
 
-// One-shot all-reduce launch shape.  Starts from the shared rule above; with
-// 2, 4 or 8 ranks a forced 8 vectors per thread is kept (other rank counts
-// have no such kernel and get 4).
+// All-reduce launch shape by the shared rule above; with 2, 4 or 8 ranks a
+// forced 8 vectors per thread is kept (other rank counts have no such kernel
+// and get 4).  The split all-reduce and launches under a workgroup cap run it
+// as it is.
 //
-// Sizes of a few MiB per rank with 2, 4, 8 and 16 ranks have shapes of their
-// own, by quarter MiB per rank and dtype.  What decides there is how full the
+// 8 ranks, 8-32 MiB per rank: 8 vectors per thread in 256-thread workgroups.
+// That kernel holds 256 VGPRs, so one workgroup per CU runs at a time and
+// the launch proceeds in rounds of 256 workgroups, each moving 32 KiB
+// contiguous per rank buffer.  Measured on MI355X it was 5-8 % faster than
+// the rest of the rule at 8 and 16 MiB per rank, when its chunks fill whole
+// rounds; with an emptier last round it lost.  So it is taken when the rounds
+// together are at least `tenths` tenths full.
+inline void eight_vector_rounds(int64_t vectors_per_rank, int tenths, int& nt, int& vpt) {
+    if (vectors_per_rank < (int64_t(1) << 19) || vectors_per_rank > (int64_t(1) << 21)) return;
+    constexpr int64_t kChunk = 256 * 8, kRound = 256;
+    const int64_t G = (vectors_per_rank + kChunk - 1) / kChunk;
+    const int64_t rounds = (G + kRound - 1) / kRound;
+    if (G * 10 >= rounds * kRound * tenths) {
+        nt = 256;
+        vpt = 8;
+    }
+}
+
+inline void shared_ar_shape(int64_t vectors_per_rank, int P, int& nt, int& vpt) {
+    nt = pick_threads(vectors_per_rank, P);
+    vpt = pick_vpt(vectors_per_rank, P);
+    if (tuning().vpt == 8 && (P == 2 || P == 4 || P == 8)) vpt = 8;
+    if (P == 8 && !tuning().wg_threads && !tuning().vpt) eight_vector_rounds(vectors_per_rank, 9, nt, vpt);
+}
+
+// One-shot all-reduce launch shape.  Sizes of a few MiB per rank have shapes
+// of their own, by quarter MiB per rank and dtype.  What decides there is how full the
 // rounds of resident workgroups are: a thread holds 16 B x ranks x vectors in
 // registers, so the launch runs in rounds of a size that the shape fixes, and
 // a mostly empty last round, or fewer waves than SIMDs, costs 10-25 %.
@@ -244,13 +295,7 @@ inline void pick_ag_shape(int64_t out_vectors, int P, int& nt, int& vpt) {
 // round it lost, and at 20 MiB (83 % full) it was 2 % slower.  So it is taken
 // when the rounds are at least 80 % full, from 16 MiB at least 90 %.
 inline void pick_ar_shape(int64_t vectors_per_rank, int P, int dtype, int& nt, int& vpt) {
-    nt = pick_threads(vectors_per_rank, P);
-    vpt = pick_vpt(vectors_per_rank, P);
-    const bool eight_ok = P == 2 || P == 4 || P == 8;
-    if (tuning().vpt == 8 && eight_ok) {
-        vpt = 8;
-        return;
-    }
+    shared_ar_shape(vectors_per_rank, P, nt, vpt);
     if (tuning().wg_threads || tuning().vpt) return;
     const bool f32 = dtype == kDtF32;
     static constexpr ShapeRow k2f[] = {{16, 64, 8}, {128, 0, 0}};
@@ -274,14 +319,7 @@ inline void pick_ar_shape(int64_t vectors_per_rank, int P, int dtype, int& nt, i
     else if (P == 8) f32 ? row_shape(k8f, v, nt, vpt) : row_shape(k8b, v, nt, vpt);
     else if (P >= 9 && P <= 15) row_shape(k15, v, nt, vpt);
     else if (P == 16) f32 ? row_shape(k16f, v, nt, vpt) : row_shape(k16b, v, nt, vpt);
-    if (P != 8 || vectors_per_rank <= (int64_t(1) << 19) || vectors_per_rank > (int64_t(1) << 21)) return;
-    constexpr int64_t kChunk = 256 * 8, kRound = 256;
-    const int64_t G = (vectors_per_rank + kChunk - 1) / kChunk;
-    const int64_t rounds = (G + kRound - 1) / kRound;
-    if (G * 10 >= rounds * kRound * (vectors_per_rank < (int64_t(1) << 20) ? 8 : 9)) {
-        nt = 256;
-        vpt = 8;
-    }
+    if (P == 8 && v > (int64_t(1) << 19)) eight_vector_rounds(v, v < (int64_t(1) << 20) ? 8 : 9, nt, vpt);
 }
 
 // Threads of a row copy (rowvec 16-byte vectors, 4 per thread and pass).  One
@@ -290,7 +328,11 @@ inline void pick_ar_shape(int64_t vectors_per_rank, int P, int dtype, int& nt, i
 // ranks, 512 tokens, bf16, top-8, with 256 / 128 / 64 threads: 128 vectors
 // 16.7 / 12.7 / 8.9 us, 256 vectors 24.6 / 17.0 / 17.3, 360 vectors 25.2 / 23.4 /
 // 23.8, 512 vectors 31.8 / 32.5 / 34.8, 896 vectors 57.2 / 58.5 / 59.4.
-inline int pick_row_threads(int64_t rowvec) { return rowvec <= 256 ? 64 : rowvec < 512 ? 128 : kWG; }
+// Under a caller's workgroup cap, 256 (cap 64, 300 tokens of 256 vectors,
+// top-2: 40.5 us with 256, 43.9 with 64).
+inline int pick_row_threads(int64_t rowvec, bool capped) {
+    return capped ? kWG : rowvec <= 256 ? 64 : rowvec < 512 ? 128 : kWG;
+}
 
 constexpr int kRowVpt = 4;
 

@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 import oracle
-from gpu_util import assert_bitwise, to_dev, to_host
+from gpu_util import assert_bitwise, run_combine, to_dev, to_host
 from test_gpu_parity import run_allreduce
 from paper_2608_00867_amd import workloads as wl
 
@@ -128,3 +128,65 @@ def test_tails_of_many_ranks(nuna, P):
     for dtype in ("bf16", "f32"):
         for n in (3, 16 * (16 // ES[dtype]) + 1, 5003):
             _allreduce(nuna, P, dtype, n, f"tail P={P} {dtype} n={n}")
+
+
+# ---------------------------------------------------------------- shapes under a workgroup cap
+
+def test_capped_all_reduce_and_reduce_scatter_shapes(nuna):
+    """A capped launch loops over its items in few workgroups: they are of 256 threads (or hold 4 and more vectors),
+    not the one-wave workgroups that fill the chip otherwise, and 9 to 15 ranks leave the tile kernel."""
+    cases = [(6, "bf16", 3 * MIB // 4, (256, 1)), (6, "f32", 3 * MIB // 8, (256, 1)), (8, "f32", 9 * MIB // 16, (256, 1)),
+             (8, "bf16", 2 * MIB, (256, 2)), (16, "bf16", 9 * MIB // 8, (256, 1)), (2, "f32", MIB, (128, 4)),
+             (12, "f32", 3 * MIB // 2, (128, 4)), (8, "bf16", 4 * MIB, (256, 8))]
+    nuna.set_max_workgroups(64)
+    try:
+        for P, dtype, n, shape in cases:
+            rec = _allreduce(nuna, P, dtype, n + 3, f"cap AR P={P} {dtype} n={n}")
+            assert (rec["threads"], rec["vectors_per_thread"]) == shape and rec["grid"] <= 64, (P, dtype, n, rec)
+        rec = _allreduce(nuna, 12, "bf16", MIB // 8, "cap AR 12 ranks")
+        assert rec["kernels"] == "k_allreduce_direct" and rec["threads"] == 256 and rec["grid"] <= 64, rec
+        for P, dtype, m in ((4, "bf16", 3 * MIB // 16), (6, "f32", MIB // 16), (8, "bf16", MIB // 16),
+                            (8, "f32", MIB // 64), (12, "bf16", MIB // 16), (16, "f32", MIB // 128)):
+            x = _values(P, P * m, dtype, 11 * P)
+            outs = nuna.reduce_scatter([to_dev(a) for a in x])
+            rec = nuna.last_launch()
+            torch.cuda.synchronize()
+            ref = oracle.reduce_scatter(x)
+            for r in (0, P - 1):
+                assert_bitwise(to_host(outs[r]), ref[r], f"cap RS P={P} {dtype} rank {r}")
+            assert rec["threads"] == 256 and rec["grid"] <= 64, (P, dtype, m, rec)
+    finally:
+        nuna.set_max_workgroups(0)
+    assert _allreduce(nuna, 6, "bf16", 3 * MIB // 4, "uncapped")["threads"] == 64
+
+
+def test_capped_moe_shapes(nuna):
+    """Short rows under a cap keep 256 threads, and the combine from lists 2 vectors per thread."""
+    P, T, k, E, H = 16, 40, 4, 64, 2048
+    topk = wl.moe_routing(P, T, k, E, 5)
+    send_np = wl.moe_rows(P, T, H, 6)
+    ref = oracle.all_to_all(send_np, topk, E)
+    back = oracle.combine(ref, topk, E, None)
+    lay = nuna.A2ALayout(topk, E).upload()
+    rows = [int(v) for v in lay.recv_rows()]
+    recv = [torch.zeros((max(rows), H), dtype=torch.bfloat16, device="cuda") for _ in range(P)]
+    send = [to_dev(a.reshape(-1)).view(T, H) for a in send_np]
+    topk_dev = torch.from_numpy(np.ascontiguousarray(topk)).cuda()
+    counts = torch.zeros(P + 1, dtype=torch.int64, device="cuda")
+    for cap, threads in ((40, 256), (0, 64)):
+        nuna.set_max_workgroups(cap)
+        try:
+            nuna.all_to_all(send, recv, lay, placement="linear")
+            assert nuna.last_launch()["threads"] == threads, nuna.last_launch()
+            nuna.all_to_all_routed(send, recv, topk_dev, E, counts, placement="linear")
+            assert nuna.last_launch()["threads"] == threads, nuna.last_launch()
+            torch.cuda.synchronize()
+            for d in range(P):
+                assert_bitwise(to_host(recv[d])[:rows[d]], ref[d], f"cap {cap} dispatch rank {d}")
+            got = run_combine(nuna, ref, topk, E, "linear")
+            assert nuna.last_launch()["vectors_per_thread"] == (2 if cap else 1), nuna.last_launch()
+        finally:
+            nuna.set_max_workgroups(0)
+        for s in range(P):
+            assert_bitwise(got[s], back[s], f"cap {cap} combine rank {s}")
+    lay.close()
