@@ -734,7 +734,8 @@ hipError_t launch_allreduce(const void* const* in, void* const* out, int P, size
     const int gsize = dest_groups > 1 ? dest_groups : 1;
     s.dpi = P / gsize;
     int nt, vpt;
-    pick_ar_shape(s.nvec, P, dtype, nt, vpt);
+    if (gsize > 1) pick_split_shape(s.nvec, P, dtype, nt, vpt);
+    else pick_ar_shape(s.nvec, P, dtype, nt, vpt);
     if (grid_capped((s.nvec + static_cast<int64_t>(nt) * vpt - 1) / (static_cast<int64_t>(nt) * vpt) * gsize)) {
         shared_ar_shape(s.nvec, P, nt, vpt);
         if (gsize == 1 && dtype == kDtBf16 && nt == 128 && vpt == 4 && !tuning().wg_threads && !tuning().vpt) {

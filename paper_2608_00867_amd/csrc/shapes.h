@@ -322,6 +322,36 @@ inline void pick_ar_shape(int64_t vectors_per_rank, int P, int dtype, int& nt, i
     if (P == 8 && v > (int64_t(1) << 19)) eight_vector_rounds(v, v < (int64_t(1) << 20) ? 8 : 9, nt, vpt);
 }
 
+// Split all-reduce: the shared rule with fp32 and, beyond the rows below, with
+// bf16.  Its groups read every chunk several times and keep few stores per
+// thread, so the one-shot's rows do not hold for it: 8 ranks of bf16 at 3.5 MiB
+// took 18.4 us with the row's 64x8 and 14.0 with 256x1, at 7 MiB 36.8 (256x8) and
+// 28 (128x4); 3 ranks at 3 MiB 7.8 (64x4) and 6.6 (256x1); 16 ranks at 3.5 MiB 35
+// (64x4) and 27 (256x1); 5-7 ranks of fp32 7-9 % more with 256x4.  Those kept
+// measured at the shared rule's time or less: 2 ranks below 8 MiB 4.25 -> 3.67 us
+// (64x8, 4 MiB), 6 ranks 46.6 -> 39.5 (256x4, 8 MiB), 12 ranks 51.6 -> 35.1
+// (128x2, 6 MiB; fp32 36.9 -> 27.5).
+inline void pick_split_shape(int64_t vectors_per_rank, int P, int dtype, int& nt, int& vpt) {
+    shared_ar_shape(vectors_per_rank, P, nt, vpt);
+    if (tuning().wg_threads || tuning().vpt) return;
+    const int64_t v = vectors_per_rank;
+    const bool f32 = dtype == kDtF32;
+    static constexpr ShapeRow k2b[] = {{13, 64, 8}, {32, 0, 0}};
+    static constexpr ShapeRow k4b[] = {{14, 256, 2}, {16, 128, 4}, {24, 64, 8}, {48, 0, 0}};
+    static constexpr ShapeRow k7b[] = {{5, 64, 1}, {7, 0, 0}, {28, 256, 4}, {56, 0, 0}};
+    static constexpr ShapeRow k8b[] = {{9, 128, 2}, {13, 0, 0}};
+    static constexpr ShapeRow k15b[] = {{18, 128, 2}, {30, 256, 4}, {38, 128, 2}, {56, 0, 0}};
+    static constexpr ShapeRow k15f[] = {{18, 128, 2}, {30, 0, 0}, {38, 128, 2}, {56, 0, 0}};
+    static constexpr ShapeRow k16[] = {{20, 128, 2}, {26, 0, 0}, {34, 128, 2}, {64, 0, 0}};
+    if (P >= 9 && P <= 15) f32 ? row_shape(k15f, v, nt, vpt) : row_shape(k15b, v, nt, vpt);
+    else if (P == 16) row_shape(k16, v, nt, vpt);
+    if (f32) return;
+    if (P == 2) row_shape(k2b, v, nt, vpt);
+    else if (P == 4) row_shape(k4b, v, nt, vpt);
+    else if (P >= 5 && P <= 7) row_shape(k7b, v, nt, vpt);
+    else if (P == 8 && v < (int64_t(1) << 19)) row_shape(k8b, v, nt, vpt);
+}
+
 // Threads of a row copy (rowvec 16-byte vectors, 4 per thread and pass).  One
 // workgroup copies one row, and with short rows the setup of its waves is what
 // the launch costs: as few waves as the row fills in one pass.  Dispatch of 8

@@ -190,3 +190,17 @@ def test_capped_moe_shapes(nuna):
         for s in range(P):
             assert_bitwise(got[s], back[s], f"cap {cap} combine rank {s}")
     lay.close()
+
+
+# ---------------------------------------------------------------- split and two-shot shapes
+
+@pytest.mark.parametrize("P,dtype,mib,shape", [(8, "bf16", 3.5, (256, 1)), (8, "bf16", 7, (128, 4)), (8, "f32", 7, (128, 4)),
+                                               (3, "bf16", 3, (256, 1)), (16, "bf16", 3.5, (256, 1)),
+                                               (16, "f32", 2.5, (256, 1)), (6, "f32", 8, (128, 4)), (6, "bf16", 8, (256, 4)),
+                                               (12, "bf16", 3, (256, 1)), (12, "bf16", 6, (128, 2)), (2, "bf16", 4, (64, 8)),
+                                               (2, "bf16", 8, (128, 4))])
+def test_split_all_reduce_shapes(nuna, P, dtype, mib, shape):
+    """The split all-reduce has the shared rule's shapes, not the one-shot's, except where those measured faster."""
+    rec = _allreduce(nuna, P, dtype, int(mib * MIB) // ES[dtype], f"split P={P} {dtype} {mib} MiB", algo="one_shot_split",
+                     check=mib <= 4)
+    assert (rec["threads"], rec["vectors_per_thread"]) == shape, rec
