@@ -826,8 +826,7 @@ bool two_shot_runs_fused(int P, size_t count, int dtype) {
 }
 
 // Fused two-shot all-reduce (k_two_shot_direct / k_two_shot): launch shape by
-// the bytes per rank, as for the one-shot (the two move the same bytes);
-// chunks are cut per shard.
+// the bytes per rank; chunks are cut per shard.
 hipError_t launch_two_shot_fused(const void* const* in, void* const* out, int P, size_t count, int dtype, int mode,
                                  hipStream_t stream) {
     if (!two_shot_fused_ok(P, count, dtype)) return hipErrorInvalidValue;
@@ -835,10 +834,16 @@ hipError_t launch_two_shot_fused(const void* const* in, void* const* out, int P,
     const size_t bytes = count * es;
     const int64_t nvec = static_cast<int64_t>(bytes / 16);
     const int64_t mv = nvec / P;
+    // The one-shot's shapes, but the shared rule under a workgroup cap and where
+    // the rows measured slower here: 2 ranks of fp32 up to 8 MiB per rank (64x8,
+    // 8 MiB: 5.73 us against 5.46 with 128x4), 4 ranks of bf16 at 3.25-3.5 MiB
+    // (256x2 5.36, 256x1 5.16).
     int nt, vpt;
     pick_ar_shape(nvec, P, dtype, nt, vpt);
+    const bool shared = (P == 2 && dtype == kDtF32 && bytes <= (size_t(8) << 20)) ||
+                        (P == 4 && dtype == kDtBf16 && bytes < (size_t(7) << 19));
     const int64_t row_cv = static_cast<int64_t>(nt) * vpt;
-    if (grid_capped((mv + row_cv - 1) / row_cv * P)) shared_ar_shape(nvec, P, nt, vpt);
+    if (shared || grid_capped((mv + row_cv - 1) / row_cv * P)) shared_ar_shape(nvec, P, nt, vpt);
     if (vpt == 8 && P == 16) vpt = 4;
     const int64_t cv = static_cast<int64_t>(nt) * vpt;
     const int64_t wcs = (mv + cv - 1) / cv;

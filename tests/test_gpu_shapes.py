@@ -204,3 +204,11 @@ def test_split_all_reduce_shapes(nuna, P, dtype, mib, shape):
     rec = _allreduce(nuna, P, dtype, int(mib * MIB) // ES[dtype], f"split P={P} {dtype} {mib} MiB", algo="one_shot_split",
                      check=mib <= 4)
     assert (rec["threads"], rec["vectors_per_thread"]) == shape, rec
+
+
+@pytest.mark.parametrize("P,dtype,mib,shape", [(2, "f32", 4, (128, 4)), (2, "f32", 8, (128, 4)), (2, "f32", 8.25, (64, 8)),
+                                               (4, "bf16", 3.25, (256, 1)), (4, "bf16", 3.5, (256, 2))])
+def test_fused_two_shot_shapes(nuna, P, dtype, mib, shape):
+    rec = _allreduce(nuna, P, dtype, int(mib * MIB) // ES[dtype], f"two-shot P={P} {dtype} {mib} MiB", algo="two_shot",
+                     check=mib <= 4)
+    assert rec["kernels"] == "k_two_shot_direct" and (rec["threads"], rec["vectors_per_thread"]) == shape, rec
