@@ -650,6 +650,14 @@ hipError_t launch_reduce_scatter(const void* const* in, void* const* out, int P,
     const int64_t row_cv = static_cast<int64_t>(nt) * vpt;
     if (grid_capped((s.mv + row_cv - 1) / row_cv * P)) {
         pick_rs_capped_shape(s.mv * P, P, dtype, nt, vpt);
+    } else if (keep_output && P <= 16 && !tuning().wg_threads && !tuning().vpt && s.mv * P >= (int64_t(1) << 17) &&
+               s.mv * P < (int64_t(1) << 18) && row_cv != kWG) {
+        // The all-gather that follows cuts these sizes (2-4 MiB per rank) into chunks of 256
+        // vectors: cut alike, a chunk is read on the XCD that wrote it, from its L2.  Two-shot of two
+        // kernels at 3 MiB, 6 ranks, 9.63 us with the standalone row's 64x1 and 9.15 with 256x1; 16 ranks
+        // at 2 MiB 13.55 (256x2) and 12.72.
+        nt = kWG;
+        vpt = 1;
     }
     const int64_t cv = static_cast<int64_t>(nt) * vpt;
     s.wcs = (s.mv + cv - 1) / cv;

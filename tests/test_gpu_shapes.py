@@ -212,3 +212,10 @@ def test_fused_two_shot_shapes(nuna, P, dtype, mib, shape):
     rec = _allreduce(nuna, P, dtype, int(mib * MIB) // ES[dtype], f"two-shot P={P} {dtype} {mib} MiB", algo="two_shot",
                      check=mib <= 4)
     assert rec["kernels"] == "k_two_shot_direct" and (rec["threads"], rec["vectors_per_thread"]) == shape, rec
+
+
+@pytest.mark.parametrize("P,n", [(6, 6 * 131072), (6, 6 * 87384), (16, MIB // 2)])
+def test_two_shot_of_two_kernels_at_2_to_4_mib(nuna, P, n):
+    """The sizes whose reduce-scatter phase is cut as its all-gather phase is."""
+    for dtype in ("bf16", "f32"):
+        _allreduce(nuna, P, dtype, n * 4 // ES[dtype], f"two kernels P={P} {dtype}", algo="two_shot_two_kernels")
