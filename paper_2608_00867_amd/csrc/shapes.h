@@ -136,7 +136,7 @@ inline bool grid_capped(int64_t items) { return items > grid_limit(INT64_MAX); }
 // Launch shapes by size: rows in quarter MiB (per rank, as the rule using them
 // says), each row holding from its size on; nt 0 leaves the shape as it was.
 struct ShapeRow {
-    int32_t from;
+    float from;
     int32_t nt, vpt;
 };
 
@@ -145,7 +145,7 @@ void row_shape(const ShapeRow (&rows)[N], int64_t vectors, int& nt, int& vpt) {
     constexpr int64_t kQuarter = int64_t(1) << 14;  // vectors in a quarter MiB
     const ShapeRow* hit = nullptr;
     for (const ShapeRow& r : rows)
-        if (r.from * kQuarter <= vectors) hit = &r;
+        if (static_cast<int64_t>(r.from * kQuarter) <= vectors) hit = &r;
     if (hit && hit->nt > 0) {
         nt = hit->nt;
         vpt = hit->vpt;
@@ -280,44 +280,46 @@ inline void shared_ar_shape(int64_t vectors_per_rank, int P, int& nt, int& vpt) 
 //   16 ranks bf16  1.5 MiB 10.2 -> 8.7 (256x2),    2.5 MiB 17.3 -> 13.6 (64x2), 3.5 MiB 23.8 -> 19.7 (64x4)
 // Each row begins where it stopped losing (2 ranks of f32 at 3.25 MiB: 64x8
 // 3.4 against 2.9 us; 4 ranks of bf16 at 3.25-3.75 MiB: 256x2 5.1-5.6 us, 64x8
-// 5.6-6.1, the shared 256x1 5.9-6.6).
+// 5.6-6.1, the shared 256x1 5.9-6.6) and ends where it starts to (16 ranks at
+// 2.02-2.2 MiB: 256x2 14.8-15.8 us, 256x1 14.1-15.4).
 // Rank counts without rows of their own in this list run the kernels with a
 // run-time count:
 //   3 ranks        3 MiB 4.33 -> 3.92 (64x4)
-//   5-7 ranks      1.5 MiB 4.1-5.0 -> 3.6-4.7 (64x1), 8 MiB 15.4-22.9 -> 15.0-21.2 (256x4)
-//   9-15 ranks     3 MiB 14.3 -> 12.9 (128x2), 6 MiB 30.8 -> 27.2 (128x2)
-// 8 ranks, 8-32 MiB per rank: 8 vectors per thread in 256-thread workgroups.
-// That kernel holds 256 VGPRs, so one workgroup per CU runs at a time and
-// the launch proceeds in rounds of 256 workgroups, each moving 32 KiB
-// contiguous per rank buffer.  Measured on MI355X it was 5-8 % faster than
-// the shared rule at 8 and 16 MiB per rank, when its chunks fill whole
-// rounds, and 5-13 % at 13 MiB, where they fill 81 %; with an emptier last
-// round it lost, and at 20 MiB (83 % full) it was 2 % slower.  So it is taken
-// when the rounds are at least 80 % full, from 16 MiB at least 90 %.
+//   5-7 ranks      1.5 MiB 4.1-5.0 -> 3.6-4.7 (64x1; with fp32 from 1.1 to 2.8 MiB, where 256x1 is
+//                  the slower one: 7 ranks at 1.2 MiB 4.2 and 3.4), 8 MiB 15.4-22.9 -> 15.0-21.2 (256x4)
+//   9-15 ranks     3 MiB 14.3 -> 12.9 (128x2), 6 MiB 30.8 -> 27.2 (128x2); with fp32 at 6.5-7.5 MiB the
+//                  shared 128x4 (26.4-35 against 27.6-36) and past 8 MiB, two rounds of 256x4, too
+// The 8-rank 256x8 is taken when its rounds are at least 80 % full, from 16 MiB
+// at least 90 %: 5-13 % faster at 13 MiB, where they are 81 % full, and 2 %
+// slower at 20 MiB (83 %).
 inline void pick_ar_shape(int64_t vectors_per_rank, int P, int dtype, int& nt, int& vpt) {
     shared_ar_shape(vectors_per_rank, P, nt, vpt);
     if (tuning().wg_threads || tuning().vpt) return;
     const bool f32 = dtype == kDtF32;
     static constexpr ShapeRow k2f[] = {{16, 64, 8}, {128, 0, 0}};
-    static constexpr ShapeRow k2b[] = {{13, 64, 8}, {128, 0, 0}};
+    static constexpr ShapeRow k2b[] = {{14.2f, 64, 8}, {128, 0, 0}};
     static constexpr ShapeRow k4f[] = {{13, 64, 8}, {80, 0, 0}};
     static constexpr ShapeRow k4b[] = {{13, 256, 2}, {16, 128, 4}, {20, 64, 8}, {90, 0, 0}};
     static constexpr ShapeRow k8f[] = {{9, 64, 4}, {13, 64, 8}, {26, 256, 8}, {33, 64, 4}, {64, 0, 0}};
     static constexpr ShapeRow k8b[] = {{9, 128, 2}, {13, 64, 8}, {26, 256, 8}, {33, 64, 4}, {64, 0, 0}};
-    static constexpr ShapeRow k16f[] = {{5, 256, 2}, {9, 64, 4}, {15, 0, 0}, {20, 128, 2}, {26, 0, 0}, {34, 128, 2},
-                                        {64, 0, 0}};
-    static constexpr ShapeRow k16b[] = {{5, 256, 2}, {9, 64, 2}, {13, 64, 4}, {15, 0, 0}, {20, 128, 2}, {26, 0, 0},
+    static constexpr ShapeRow k16f[] = {{5, 256, 2}, {8.05f, 0, 0}, {9, 64, 4}, {15, 0, 0}, {20, 128, 2}, {26, 0, 0},
                                         {34, 128, 2}, {64, 0, 0}};
+    static constexpr ShapeRow k16b[] = {{5, 256, 2}, {8.05f, 0, 0}, {9, 64, 2}, {13, 64, 4}, {15, 0, 0},
+                                        {20, 128, 2}, {26, 0, 0}, {34, 128, 2}, {64, 0, 0}};
     static constexpr ShapeRow k3[] = {{10, 64, 4}, {14, 0, 0}};
-    static constexpr ShapeRow k7[] = {{5, 64, 1}, {7, 0, 0}, {28, 256, 4}, {56, 0, 0}};
-    static constexpr ShapeRow k15[] = {{10, 128, 2}, {14, 0, 0}, {18, 128, 2}, {30, 256, 4}, {38, 128, 2}, {56, 0, 0}};
+    static constexpr ShapeRow k7f[] = {{4.5f, 64, 1}, {11.5f, 0, 0}, {28, 256, 4}, {56, 0, 0}};
+    static constexpr ShapeRow k7b[] = {{5, 64, 1}, {7, 0, 0}, {28, 256, 4}, {56, 0, 0}};
+    static constexpr ShapeRow k15f[] = {{10, 128, 2}, {14, 0, 0}, {18, 128, 2}, {26, 0, 0}, {30, 256, 4},
+                                        {32.05f, 0, 0}, {38, 128, 2}, {56, 0, 0}};
+    static constexpr ShapeRow k15b[] = {{10, 128, 2}, {14, 0, 0}, {18, 128, 2}, {30, 256, 4}, {38, 128, 2},
+                                        {56, 0, 0}};
     const int64_t v = vectors_per_rank;
     if (P == 2) f32 ? row_shape(k2f, v, nt, vpt) : row_shape(k2b, v, nt, vpt);
     else if (P == 3) row_shape(k3, v, nt, vpt);
     else if (P == 4) f32 ? row_shape(k4f, v, nt, vpt) : row_shape(k4b, v, nt, vpt);
-    else if (P >= 5 && P <= 7) row_shape(k7, v, nt, vpt);
+    else if (P >= 5 && P <= 7) f32 ? row_shape(k7f, v, nt, vpt) : row_shape(k7b, v, nt, vpt);
     else if (P == 8) f32 ? row_shape(k8f, v, nt, vpt) : row_shape(k8b, v, nt, vpt);
-    else if (P >= 9 && P <= 15) row_shape(k15, v, nt, vpt);
+    else if (P >= 9 && P <= 15) f32 ? row_shape(k15f, v, nt, vpt) : row_shape(k15b, v, nt, vpt);
     else if (P == 16) f32 ? row_shape(k16f, v, nt, vpt) : row_shape(k16b, v, nt, vpt);
     if (P == 8 && v > (int64_t(1) << 19)) eight_vector_rounds(v, v < (int64_t(1) << 20) ? 8 : 9, nt, vpt);
 }

@@ -219,3 +219,16 @@ def test_two_shot_of_two_kernels_at_2_to_4_mib(nuna, P, n):
     """The sizes whose reduce-scatter phase is cut as its all-gather phase is."""
     for dtype in ("bf16", "f32"):
         _allreduce(nuna, P, dtype, n * 4 // ES[dtype], f"two kernels P={P} {dtype}", algo="two_shot_two_kernels")
+
+
+@pytest.mark.parametrize("P,dtype,quarters,shape", [(16, "bf16", 8, (256, 2)), (16, "bf16", 8.2, (256, 1)),
+                                                    (16, "f32", 8.2, (256, 1)), (16, "f32", 9, (64, 4)),
+                                                    (11, "f32", 26, (128, 4)), (11, "f32", 32, (256, 4)),
+                                                    (11, "f32", 33, (128, 4)), (11, "bf16", 26, (128, 2)),
+                                                    (7, "f32", 4.6, (64, 1)), (7, "f32", 11, (64, 1)),
+                                                    (7, "f32", 12, (256, 1)), (7, "bf16", 8, (256, 1)),
+                                                    (2, "bf16", 13, (256, 1)), (2, "bf16", 15, (64, 8))])
+def test_one_shot_rows(nuna, P, dtype, quarters, shape):
+    n = int(quarters * (1 << 18)) // ES[dtype] // 64 * 64 + 3
+    rec = _allreduce(nuna, P, dtype, n, f"P={P} {dtype} {quarters}", check=quarters < 16)
+    assert (rec["threads"], rec["vectors_per_thread"]) == shape, rec
