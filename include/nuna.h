@@ -237,7 +237,9 @@ nuna_status_t nuna_set_max_workgroups(int max_workgroups);
  *   NUNA_STORE_GAP        pause between the stores of consecutive destinations when one
  *                         result is stored to several outputs (one-shot and fused two-shot
  *                         all-reduce, all-gather), in units of 8 wait states of the wave:
- *                         -1 (by size: 1 from 32 MiB per rank, else 0), 0..32
+ *                         -1 (by size: 1 from 32 MiB per rank; all-reduce also 2 for the
+ *                         one-shot of 16 ranks from 5 MiB and 1 for 8 ranks of bf16 at 0.9-1 MiB;
+ *                         else 0), 0..32
  * Unknown names and values outside these sets: NUNA_ERR_INVALID_ARG. */
 nuna_status_t nuna_set_tunable(const char* name, int64_t value);
 nuna_status_t nuna_get_tunable(const char* name, int64_t* value);

@@ -771,6 +771,7 @@ hipError_t launch_allreduce(const void* const* in, void* const* out, int P, size
     // One item per workgroup: the direct kernel (page-grouped in XCD mode).
     const DirectMap m = direct_map(mode, groups > 0 ? groups : 1, cv * 16);
     if (gsize == 1 && m.direct && direct_ranks(P, vpt)) {
+        s.gap = one_shot_store_gap(bytes, P, dtype);
         note_launch("k_allreduce_direct", m.gshift > 0 ? kMapXcdPages : kMapLinear, int64_t(1) << m.gshift, m.grid, nt,
                     vpt);
         if (dtype == kDtF32) {

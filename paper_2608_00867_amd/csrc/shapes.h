@@ -21,6 +21,8 @@ inline bool direct_ranks(int P, int vpt) { return P == 2 || P == 4 || P == 8 || 
 // faster than the direct one on MI355X (184 against 209 us), while up to 8192
 // workgroups the direct kernels were as fast or faster at every size measured
 // (1-64 MiB per rank, 1-4 vectors per thread).
+inline int64_t direct_max_grid() { return tuning().direct_max_grid > 0 ? tuning().direct_max_grid : 8192; }
+
 // store_gap pauses of a fan-out kernel by the bytes each output rank
 // receives: one from 32 MiB per rank (long, throughput-bound launches), none
 // below (latency-bound ones), unless the tunable fixes the count.
@@ -30,7 +32,19 @@ inline int store_gap_for(size_t bytes_per_rank) {
     return bytes_per_rank >= (size_t(32) << 20) ? 1 : 0;
 }
 
-inline int64_t direct_max_grid() { return tuning().direct_max_grid > 0 ? tuning().direct_max_grid : 8192; }
+// Pauses of the one-shot all-reduce's direct kernel.  Two more launches need them,
+// whose waves store in step: 16 ranks from 5 MiB per rank, which holds every output
+// pointer from the start (us with 0, 1 and 2 pauses, and as a kernel that loads
+// each pointer ahead of its store: 6 MiB 38.0, 35.0, 34.7, 38.9; 16 MiB 113, 106,
+// 103, 105; both fp32), and bf16 with 8 ranks at 0.9-1 MiB, one workgroup per CU
+// (1 MiB 3.61, 3.46).
+inline int one_shot_store_gap(size_t bytes_per_rank, int P, int dtype) {
+    const int g = store_gap_for(bytes_per_rank);
+    if (g > 0 || tuning().store_gap >= 0) return g;
+    if (P == 16) return bytes_per_rank >= (size_t(5) << 20) ? 2 : 0;
+    return P == 8 && dtype == kDtBf16 && bytes_per_rank > (size_t(7) << 17) && bytes_per_rank <= (size_t(1) << 20) ? 1 : 0;
+}
+
 constexpr int64_t kAgDirectMaxGrid8 = int64_t(1) << 20;  // 8-rank all-gather (launch_all_gather)
 
 // Launch of a direct kernel over `items` work items, one per workgroup.
