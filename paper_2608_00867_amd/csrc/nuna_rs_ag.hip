@@ -380,11 +380,21 @@ __global__ __launch_bounds__(kWG) void k_all_gather_direct(Ptrs<rank_cap<PT>()> 
 // kernel below is the slower one (fewer waves in flight for the same bytes): 8
 // ranks of bf16 at 32 KiB shards 2.46 against 2.66 us and at 64 KiB 2.92 against
 // 3.31, 4 ranks at 128 KiB 2.31 against 2.72; at 128 KiB shards and 8 ranks 4.18
-// against 3.79.
+// against 3.79.  With 9 to 16 ranks, where it has twice the stores per thread, in the
+// middle of that range only (12 ranks of fp32 at 32 KiB shards 3.06 against 3.40 us, at
+// 4 KiB 2.60 against 2.38, at 96 KiB 5.1 against 5.0).
 constexpr int64_t kAgRaggedElems = int64_t(1) << 19;
 
-template <int ES>
-__global__ __launch_bounds__(kWG) void k_all_gather_elem(Ptrs<8> p, int P, int64_t m) {
+inline bool ag_ragged_elem(int P, int64_t m, int64_t es) {
+    if (P <= 8) return m * P <= kAgRaggedElems;
+    const int64_t shard = m * es;
+    if (P > 16 || shard < (20 << 10)) return false;
+    if (es == 4) return shard <= (P <= 12 ? 72 << 10 : 42 << 10);
+    return P <= 12 && shard >= (P <= 10 ? 20 << 10 : 30 << 10) && shard <= (42 << 10);
+}
+
+template <int ES, int MAXP>
+__global__ __launch_bounds__(kWG) void k_all_gather_elem(Ptrs<MAXP> p, int P, int64_t m) {
     using E = typename std::conditional<ES == 2, uint16_t, uint32_t>::type;
     const int64_t total = m * P;
     for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < total;
@@ -398,6 +408,12 @@ __global__ __launch_bounds__(kWG) void k_all_gather_elem(Ptrs<8> p, int P, int64
             if (dst != src) dst[j] = v;
         }
     }
+}
+
+template <int ES, int MAXP>
+void launch_ag_elem(const void* const* in, void* const* out, int P, int64_t m, int64_t G, hipStream_t st) {
+    hipLaunchKernelGGL((k_all_gather_elem<ES, MAXP>), dim3(static_cast<unsigned>(G)), dim3(kWG), 0, st,
+                       make_ptrs<MAXP>(in, out, P, P), P, m);
 }
 
 // All-gather of ragged shards: workgroup (c, r, g) copies chunk c of shard r,
@@ -696,16 +712,12 @@ hipError_t launch_all_gather(const void* const* in, void* const* out, int P, siz
     const size_t es = dtype_size(dtype);
     if ((m * es) % 16 != 0) {
         const int64_t bytes = static_cast<int64_t>(m * es), mv = bytes / 16, total = static_cast<int64_t>(m) * P;
-        if (P <= 8 && total <= kAgRaggedElems) {
-            const Ptrs<8> p = make_ptrs<8>(in, out, P, P);
+        if (ag_ragged_elem(P, static_cast<int64_t>(m), static_cast<int64_t>(es))) {
             const int64_t G = cap_grid((total + kWG - 1) / kWG);
             note_launch("k_all_gather_elem", kMapLinear, 1, G, kWG, 0);
-            if (es == 4)
-                hipLaunchKernelGGL((k_all_gather_elem<4>), dim3(static_cast<unsigned>(G)), dim3(kWG), 0, stream, p, P,
-                                   static_cast<int64_t>(m));
-            else
-                hipLaunchKernelGGL((k_all_gather_elem<2>), dim3(static_cast<unsigned>(G)), dim3(kWG), 0, stream, p, P,
-                                   static_cast<int64_t>(m));
+            const int64_t n = static_cast<int64_t>(m);
+            if (P <= 8) es == 4 ? launch_ag_elem<4, 8>(in, out, P, n, G, stream) : launch_ag_elem<2, 8>(in, out, P, n, G, stream);
+            else es == 4 ? launch_ag_elem<4, 16>(in, out, P, n, G, stream) : launch_ag_elem<2, 16>(in, out, P, n, G, stream);
             return hipGetLastError();
         }
         int nt, vpt;
@@ -714,9 +726,9 @@ hipError_t launch_all_gather(const void* const* in, void* const* out, int P, siz
         const int64_t wcs = ragged_chunks(mv, cv);
         // Up to 4 groups while the launch is short of 1500 workgroups: 8 ranks of 128 KiB
         // shards 3.98 us against 4.73 with 8 groups and 4.60 with one.
-        const int split = wcs * P < 1500 ? largest_divisor_upto(P, 4) : 1;
-        const int groups = split <= max_workgroups() ? split : 1;
-        const int dpi = P / groups, gap = store_gap_for(m * es * P);
+        const int split = wcs * P < 1500 ? (P < 4 ? P : 4) : 1;
+        const int dpi = split <= max_workgroups() ? (P + split - 1) / split : P;
+        const int groups = (P + dpi - 1) / dpi, gap = store_gap_for(m * es * P);
         const dim3 g = ragged_grid(wcs, P, groups);
         note_launch("k_all_gather_ragged", kMapLinear, 1, int64_t(g.x) * g.y * g.z, nt, vpt);
         if (es == 4) {
