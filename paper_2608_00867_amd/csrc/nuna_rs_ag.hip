@@ -250,10 +250,17 @@ __global__ __launch_bounds__(kWG) void k_reduce_scatter_ragged(Ptrs<MAXP> p, int
 // its wide loads save up to 512 Ki elements of input per rank (6 ranks of bf16:
 // 2.3 against 2.7 us at 16 KiB shards, 10.1 against 6.4 at 512 KiB; 12 ranks of
 // fp32 6.3 against 6.7 at 128 KiB, 19.6 against 15.7 at 512 KiB).
+// 17 to 19 ranks of bf16, whose second batch of 16 holds 1 to 3, keep it up to
+// 216 Ki (17 ranks at 16 KiB shards 3.74 against 4.17 us, at 32 KiB 6.1 against 4.7).
 constexpr int64_t kRsRaggedElems = int64_t(1) << 19;
 
-template <int DT>
-__global__ __launch_bounds__(kWG) void k_reduce_scatter_elem(Ptrs<16> p, int P, int64_t m) {
+inline bool rs_ragged_elem(int P, int64_t total, int dtype) {
+    if (P < 16) return P != 2 && P != 8 && total <= kRsRaggedElems;
+    return P > 16 && P < 20 && dtype == kDtBf16 && total <= (216 << 10);
+}
+
+template <int DT, int MAXP>
+__global__ __launch_bounds__(kWG) void k_reduce_scatter_elem(Ptrs<MAXP> p, int P, int64_t m) {
     using A = Arith<DT>;
     using Raw = typename A::Raw;
     const int64_t total = m * P;
@@ -264,6 +271,12 @@ __global__ __launch_bounds__(kWG) void k_reduce_scatter_elem(Ptrs<16> p, int P, 
         for (int q = 1; q < P; ++q) a = a + A::widen1(reinterpret_cast<const Raw*>(p.in[q])[i]);
         A::store1(p.out[r], i - r * m, a);
     }
+}
+
+template <int DT, int MAXP>
+void launch_rs_elem(const void* const* in, void* const* out, int P, int64_t m, int64_t G, hipStream_t st) {
+    hipLaunchKernelGGL((k_reduce_scatter_elem<DT, MAXP>), dim3(static_cast<unsigned>(G)), dim3(kWG), 0, st,
+                       make_ptrs<MAXP>(in, out, P, P), P, m);
 }
 
 // ---------------------------------------------------------------- all-gather
@@ -633,16 +646,13 @@ hipError_t launch_reduce_scatter(const void* const* in, void* const* out, int P,
     if ((m * es) % 16 != 0) {
         const int64_t mv = static_cast<int64_t>(m * es / 16);
         const int64_t total = static_cast<int64_t>(m) * P;
-        if (P < 16 && P != 2 && P != 8 && total <= kRsRaggedElems) {
-            const Ptrs<16> p = make_ptrs<16>(in, out, P, P);
+        if (rs_ragged_elem(P, total, dtype)) {
             const int64_t G = cap_grid((total + kWG - 1) / kWG);
             note_launch("k_reduce_scatter_elem", kMapLinear, 1, G, kWG, 0);
-            if (dtype == kDtF32)
-                hipLaunchKernelGGL((k_reduce_scatter_elem<kDtF32>), dim3(static_cast<unsigned>(G)), dim3(kWG), 0,
-                                   stream, p, P, static_cast<int64_t>(m));
-            else
-                hipLaunchKernelGGL((k_reduce_scatter_elem<kDtBf16>), dim3(static_cast<unsigned>(G)), dim3(kWG), 0,
-                                   stream, p, P, static_cast<int64_t>(m));
+            const int64_t n = static_cast<int64_t>(m);
+            if (P > 16) launch_rs_elem<kDtBf16, 64>(in, out, P, n, G, stream);
+            else if (dtype == kDtF32) launch_rs_elem<kDtF32, 16>(in, out, P, n, G, stream);
+            else launch_rs_elem<kDtBf16, 16>(in, out, P, n, G, stream);
             return hipGetLastError();
         }
         int nt, vpt;

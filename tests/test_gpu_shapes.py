@@ -232,3 +232,32 @@ def test_one_shot_rows(nuna, P, dtype, quarters, shape):
     n = int(quarters * (1 << 18)) // ES[dtype] // 64 * 64 + 3
     rec = _allreduce(nuna, P, dtype, n, f"P={P} {dtype} {quarters}", check=quarters < 16)
     assert (rec["threads"], rec["vectors_per_thread"]) == shape, rec
+
+
+# ---------------------------------------------------------------- ragged shards
+
+@pytest.mark.parametrize("P", [9, 10, 13, 14, 17, 18])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_ragged_routes(nuna, P, dtype):
+    """Shards on either side of the element kernels' ranges, and destination groups that do not divide the ranks."""
+    es = ES[dtype]
+    for kib in (2, 19, 21, 41, 43, 73):
+        m = (kib << 10) // es + 1
+        what = f"P={P} {dtype} m={m}"
+        x = _values(P, P * m, dtype, 13 * P + kib)
+        ref = oracle.reduce_scatter(x)
+        outs = nuna.reduce_scatter([to_dev(a) for a in x])
+        rs = nuna.last_launch()["kernels"]
+        src = [a[:m].copy() for a in x]
+        ref_g = oracle.all_gather(src)
+        outs_g = nuna.all_gather([to_dev(a) for a in src])
+        ag = nuna.last_launch()["kernels"]
+        torch.cuda.synchronize()
+        for d in range(P):
+            assert_bitwise(to_host(outs[d]), ref[d], f"RS {what} rank {d}")
+        for d in {0, P // 2, P - 1}:
+            assert_bitwise(to_host(outs_g[d]), ref_g[d], f"AG {what} rank {d}")
+        low, high = 20, 72 if dtype == "f32" and P <= 12 else 42 if dtype == "f32" and P <= 16 or P <= 12 else 0
+        assert ag == ("k_all_gather_elem" if low <= kib < high else "k_all_gather_ragged"), (what, ag)
+        elem = P < 16 and P * m <= 1 << 19 or P > 16 and dtype == "bf16" and P * m <= 216 << 10
+        assert rs == ("k_reduce_scatter_elem" if elem else "k_reduce_scatter_ragged"), (what, rs)
