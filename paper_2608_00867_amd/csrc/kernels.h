@@ -92,6 +92,9 @@ hipError_t launch_all_to_all(const void* const* send, void* const* recv, int P, 
 // (rank, row).  rec: null, or (P <= kCombRecRanks) the same entries as
 // kCombRecRanks words per token, (row << 3) | rank, padded with all ones.
 constexpr int kCombRecRanks = 8;
+// Row copies in the layout of the combine call that the calling thread is in
+// (set by the host API): over the tokens, the rows that one token sums.
+int64_t combine_copies();
 hipError_t launch_combine(const void* const* y, void* const* out, int P, int T, const void* off, const void* ent,
                           const void* rec, const float* weights, size_t row_bytes, int dtype, int mode,
                           hipStream_t stream);

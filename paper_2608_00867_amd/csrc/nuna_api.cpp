@@ -147,6 +147,7 @@ std::once_flag g_tuning_once;
 
 // Launches of the calling thread's last collective call (nuna_last_launch).
 thread_local nuna_launch_info_t t_launch;
+thread_local int64_t t_combine_copies = 0;
 
 // Start the record of a call's launches (after its argument checks).
 void begin_launches() { std::memset(&t_launch, 0, sizeof t_launch); }
@@ -211,6 +212,8 @@ const TunableDef* find_tunable(const char* name) {
 }  // namespace
 
 namespace nuna {
+int64_t combine_copies() { return t_combine_copies; }
+
 void note_launch(const char* kernel, int map, int64_t group_size, int64_t grid, int threads, int vpt) {
     nuna_launch_info_t& r = t_launch;
     const size_t used = std::strlen(r.kernels);
@@ -894,6 +897,7 @@ nuna_status_t nuna_all_to_all_combine(const void* const* y, void* const* out, co
     if (L->nitems == 0) return ok();
     if (L->device < 0) return fail(NUNA_ERR_INVALID_ARG, "layout has not been uploaded (nuna_a2a_layout_upload)");
     if ((st = check_placement_ready(place))) return st;
+    t_combine_copies = L->nitems;
     hipError_t e = nuna::launch_combine(y, out, P, L->T, L->dev_comb_off, L->dev_comb_ent, L->dev_comb_rec, weights,
                                         row_bytes, static_cast<int>(dtype), place, stream);
     return hip_status(e, "all-to-all combine launch");

@@ -377,7 +377,17 @@ hipError_t launch_combine(const void* const* y, void* const* out, int P, int T, 
         // passes: cap 64, 16 ranks, 60 tokens x 2880, 38.1 us against 54.6.
         const int fv = tuning().combine_vpt;
         const bool capped = !rc && grid_capped(ntok * ((s.rowvec + nt - 1) / nt));
-        const int vpt = fv == 1 || fv == 2 || fv == 4 ? fv : capped ? 2 : 1;
+        int vpt = fv == 1 || fv == 2 || fv == 4 ? fv : capped ? 2 : 1;
+        if (!rc && fv == 0 && tuning().combine_chunks == 0 && s.rowvec > nt && s.rowvec < 2 * nt) {
+            // Rows of two partly filled chunks, with the lists: one chunk of 2 vectors where the work
+            // items' own loads (offsets, entries) weigh more than the second vector's wait, that is with
+            // few rows per token and some hundred tokens, and for fp32 (4 elements a vector) also
+            // with more rows.  16 ranks, 80 tokens x 1440 fp32, top-2: 5.2 us with 2 vectors, 6.0
+            // with 1; 12 ranks, 80 x 2880 bf16, top-2, 4.5 and 5.2; 16 ranks, 140 x 2880 bf16, top-8,
+            // 17.5 and 16.9; 9 ranks, 20 x 2880, 3.1 and 2.7.
+            const bool few = combine_copies() < 3 * ntok;
+            if (dtype == kDtF32 ? ntok >= 300 && (few || ntok < 1400) : few && ntok >= 500 && ntok < 2000) vpt = 2;
+        }
         s.chunks = pick_combine_chunks(ntok, s.rowvec, nt);
         s.cw = (s.rowvec + s.chunks - 1) / s.chunks;
         if (s.cw > static_cast<int64_t>(nt) * vpt && (rc || (tuning().combine_chunks == 0 && !capped))) {

@@ -261,3 +261,24 @@ def test_ragged_routes(nuna, P, dtype):
         assert ag == ("k_all_gather_elem" if low <= kib < high else "k_all_gather_ragged"), (what, ag)
         elem = P < 16 and P * m <= 1 << 19 or P > 16 and dtype == "bf16" and P * m <= 216 << 10
         assert rs == ("k_reduce_scatter_elem" if elem else "k_reduce_scatter_ragged"), (what, rs)
+
+
+# ---------------------------------------------------------------- MoE
+
+@pytest.mark.parametrize("dtype,P,T,k,vpt", [("bf16", 16, 40, 1, 2), ("bf16", 16, 40, 8, 1), ("bf16", 9, 20, 1, 1),
+                                             ("f32", 16, 40, 8, 2), ("f32", 9, 20, 8, 1)])
+def test_combine_of_rows_between_one_and_two_chunks(nuna, dtype, P, T, k, vpt):
+    """Rows of 360 vectors from offset lists: one chunk of 2 vectors with few rows per token, else two chunks."""
+    E = 8 * P
+    H = 360 * (16 // ES[dtype])
+    topk = wl.moe_routing(P, T, k, E, 3 * P)
+    lay = nuna.A2ALayout(topk, E)
+    rows = [int(v) for v in lay.recv_rows()]
+    lay.close()
+    y = wl.result_rows(rows, H, np.uint16 if dtype == "bf16" else np.float32, 4)
+    for w in (None, wl.gate_weights(topk, E, 9)):
+        got = run_combine(nuna, y, topk, E, "xcd", weights=w)
+        assert nuna.last_launch()["vectors_per_thread"] == vpt, nuna.last_launch()
+        want = oracle.combine(y, topk, E, w)
+        for s in range(P):
+            assert_bitwise(got[s], want[s], f"combine {dtype} P={P} k={k} w={w is not None} rank {s}")
