@@ -206,8 +206,8 @@ nuna_status_t nuna_set_max_workgroups(int max_workgroups);
  *   NUNA_VPT              vectors per thread of the all-reduce, reduce-scatter and
  *                         all-gather: 0 (by size), 1, 2, 4, 8 (8: one-shot all-reduce
  *                         with 2, 4 or 8 ranks only; 4 elsewhere)
- *   NUNA_LPR_MIN_RANKS    many-rank all-reduce kernels from this many ranks, 1..65 (16, at which
- *                         9 to 15 ranks run them too)
+ *   NUNA_LPR_MIN_RANKS    many-rank all-reduce kernels from this many ranks, 1..65 (9; 9 to 15
+ *                         ranks run them only while NUNA_WG_THREADS and NUNA_VPT are 0)
  *   NUNA_LPR_MAX_VECTORS  lane-per-rank all-reduce up to this many input vectors in
  *                         total, 0..2^40 (0: never)
  *   NUNA_COMBINE_VPT      combine vectors per thread: 0 (default), 1, 2, 4

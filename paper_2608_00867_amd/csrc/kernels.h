@@ -16,7 +16,7 @@ constexpr int kDtBf16 = 1;
 inline size_t dtype_size(int dt) { return dt == kDtF32 ? 4u : 2u; }
 
 // Default rank count from which the many-rank all-reduce kernels run.
-constexpr int kManyRanks = 16;
+constexpr int kManyRanks = 9;
 
 // Tunables (read once from the environment by the host API; they change the
 // launch shape only, never the arithmetic).

@@ -711,11 +711,13 @@ hipError_t launch_allreduce(const void* const* in, void* const* out, int P, size
     // below the one-shot kernel at 64 ranks and below the lane-per-rank kernel
     // at every size; beyond that the one-shot kernel's long per-thread streams
     // win.  The lane-per-rank kernel runs only when its tunable asks for it.
-    // 9 to 15 ranks take the tile kernel too, unless the tunable says from where
-    // (12 ranks of bf16: 2.30 against 3.29 us at 64 KiB per rank, 3.49 against
-    // 4.19 at 256 KiB; up to 8 ranks the direct kernel is faster).
+    // From 9 ranks (12 ranks of bf16: 2.30 against 3.29 us at 64 KiB per rank,
+    // 3.49 against 4.19 at 256 KiB; up to 8 ranks the direct kernel is faster),
+    // or from the tunable's count; with the default count a caller's threads or
+    // vectors per thread keep the direct kernel below 16 ranks.
     const int many = tuning().lpr_min_ranks;
-    if (dest_groups <= 1 && (P >= many || (many == kManyRanks && P > 8))) {
+    const bool shaped = P < 16 && many == kManyRanks && (tuning().wg_threads || tuning().vpt);
+    if (dest_groups <= 1 && P >= many && !shaped) {
         if (static_cast<int64_t>(bytes / 16) * P <= tuning().lpr_max_vectors)
             return launch_allreduce_lpr(in, out, P, count, dtype, mode, stream);
         int tv = tuning().tile_v;

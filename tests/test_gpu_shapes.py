@@ -234,6 +234,24 @@ def test_one_shot_rows(nuna, P, dtype, quarters, shape):
     assert (rec["threads"], rec["vectors_per_thread"]) == shape, rec
 
 
+# ---------------------------------------------------------------- tunables
+
+def test_many_rank_tunable_says_from_where(nuna):
+    """9 to 15 ranks run the tile kernel by default and not when the tunable names a higher count, 16 among them, nor
+    when the caller fixes the threads or the vectors; 16 ranks run it in each case."""
+    n = 64 << 10 >> 1
+    assert _allreduce(nuna, 12, "bf16", n, "default")["kernels"] == "k_allreduce_tile_direct"
+    for tune, shape in ((dict(NUNA_LPR_MIN_RANKS=16), None), (dict(NUNA_LPR_MIN_RANKS=13), None),
+                        (dict(NUNA_VPT=2), (64, 2)), (dict(NUNA_WG_THREADS=128), (128, 1))):
+        with nuna.tunables(**tune):
+            rec = _allreduce(nuna, 12, "bf16", n, str(tune))
+            assert rec["kernels"] == "k_allreduce_direct", (tune, rec)
+            assert shape is None or (rec["threads"], rec["vectors_per_thread"]) == shape, (tune, rec)
+            assert _allreduce(nuna, 16, "bf16", n, f"16 ranks {tune}")["kernels"] == "k_allreduce_tile_direct"
+    with nuna.tunables(NUNA_LPR_MIN_RANKS=12, NUNA_VPT=2):
+        assert _allreduce(nuna, 12, "bf16", n, "named")["kernels"] == "k_allreduce_tile_direct"
+
+
 # ---------------------------------------------------------------- ragged shards
 
 @pytest.mark.parametrize("P", [9, 10, 13, 14, 17, 18])
