@@ -232,7 +232,7 @@ nuna_status_t nuna_set_max_workgroups(int max_workgroups);
  *                         mode with 16 ranks, where it measured faster), 1 (never), 2 (in
  *                         both modes with 8 or 16 ranks)
  *   NUNA_TWO_SHOT_FORM    NUNA_ALGO_TWO_SHOT: 0 (by size: fused, except 8 ranks of bf16
- *                         at 16-40 MiB per rank, which run the two kernels), 1 (fused
+ *                         above 16 and to 40 MiB per rank, which run the two kernels), 1 (fused
  *                         wherever it applies), 2 (always the two kernels)
  *   NUNA_STORE_GAP        pause between the stores of consecutive destinations when one
  *                         result is stored to several outputs (one-shot and fused two-shot

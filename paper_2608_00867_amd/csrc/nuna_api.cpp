@@ -418,10 +418,10 @@ namespace {
 
 // NUNA_ALGO_AUTO: the two-shot for 8 ranks of bf16 from 16 MiB per rank
 // (fused or two kernels, two_shot_runs_fused), the one-shot elsewhere.
-// Measured on MI355X, cold, per call: 46.2-46.6 against 47.9-48.2 us at
-// 16 MiB per rank, 177-179 against 179-181 at 64 MiB, 380-390 against
-// 386-421 at 128 MiB; at 4 MiB the one-shot leads (11.4-11.6 against
-// 11.6-11.7 us), as at every smaller size.
+// Measured on MI355X, cold, per call, two-shot against one-shot: 46.3-46.7
+// against 45.2-47.0 us at 16 MiB per rank, 54.4 against 53.8-57.4 at 18, 71.5
+// against 70.5-75.5 at 24, 95-98 against 97-100 at 32, 184-186 against 182-190 at
+// 64; below, the one-shot leads by a little (10.7 against 10.8 at 4 MiB).
 bool auto_two_shot(int P, size_t count, int dtype) {
     return P == 8 && dtype == nuna::kDtBf16 && count * nuna::dtype_size(dtype) >= (size_t(16) << 20) &&
            nuna::two_shot_fused_ok(P, count, dtype);

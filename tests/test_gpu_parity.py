@@ -534,12 +534,15 @@ def _kernels(nuna, x, algo, place):
 def test_launch_record_names_what_ran(nuna):
     """nuna_last_launch: the two-shot's form by size and its tunable, the page-grouped map in XCD mode,
     the destination-split groups, the per-XCD lists of the dispatch."""
-    x16 = wl.normal_bf16(8, 1024 * 8192, 3)  # 16 MiB per rank
-    assert _kernels(nuna, x16, "two_shot", "xcd")["kernels"] == "k_reduce_scatter_direct+k_all_gather_direct"
+    x20 = wl.normal_bf16(8, 1280 * 8192, 3)  # 20 MiB per rank
+    assert _kernels(nuna, x20, "two_shot", "xcd")["kernels"] == "k_reduce_scatter_direct+k_all_gather_direct"
     with nuna.tunables(NUNA_TWO_SHOT_FORM=1):
-        assert _kernels(nuna, x16, "two_shot", "xcd")["kernels"] == "k_two_shot_direct"
+        assert _kernels(nuna, x20, "two_shot", "xcd")["kernels"] == "k_two_shot_direct"
     # AUTO: the two-shot for 8 ranks of bf16 from 16 MiB per rank, the one-shot below
-    assert _kernels(nuna, x16, "auto", "xcd")["kernels"] == "k_reduce_scatter_direct+k_all_gather_direct"
+    assert _kernels(nuna, x20, "auto", "xcd")["kernels"] == "k_reduce_scatter_direct+k_all_gather_direct"
+    x16 = wl.normal_bf16(8, 1024 * 8192, 3)  # 16 MiB per rank
+    assert _kernels(nuna, x16, "two_shot", "xcd")["kernels"] == "k_two_shot_direct"
+    assert _kernels(nuna, x16, "auto", "xcd")["kernels"] == "k_two_shot_direct"
     x4 = wl.ar_bf16_prefill(256)
     assert _kernels(nuna, x4, "auto", "xcd")["kernels"] == "k_allreduce_direct"
     r = _kernels(nuna, x4, "two_shot", "xcd")

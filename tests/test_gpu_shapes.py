@@ -207,7 +207,8 @@ def test_split_all_reduce_shapes(nuna, P, dtype, mib, shape):
 
 
 @pytest.mark.parametrize("P,dtype,mib,shape", [(2, "f32", 4, (128, 4)), (2, "f32", 8, (128, 4)), (2, "f32", 8.25, (64, 8)),
-                                               (4, "bf16", 3.25, (256, 1)), (4, "bf16", 3.5, (256, 2))])
+                                               (4, "bf16", 3.25, (256, 1)), (4, "bf16", 3.5, (256, 2)),
+                                               (8, "bf16", 16, (256, 8))])
 def test_fused_two_shot_shapes(nuna, P, dtype, mib, shape):
     rec = _allreduce(nuna, P, dtype, int(mib * MIB) // ES[dtype], f"two-shot P={P} {dtype} {mib} MiB", algo="two_shot",
                      check=mib <= 4)
