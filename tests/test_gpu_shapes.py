@@ -301,3 +301,27 @@ def test_combine_of_rows_between_one_and_two_chunks(nuna, dtype, P, T, k, vpt):
         want = oracle.combine(y, topk, E, w)
         for s in range(P):
             assert_bitwise(got[s], want[s], f"combine {dtype} P={P} k={k} w={w is not None} rank {s}")
+
+
+def test_layout_tables_beyond_one_staged_copy(nuna):
+    """A layout of more than 16 MiB of tables, which go up one by one: dispatch and combine against the oracle."""
+    P, T, k, E, H = 8, 9000, 8, 64, 8
+    topk = wl.moe_routing(P, T, k, E, 71)
+    lay = nuna.A2ALayout(topk, E).upload()
+    rows = [int(v) for v in lay.recv_rows()]
+    assert 40 * sum(rows) + 40 * P * T > 16 * MIB
+    send_np = wl.moe_rows(P, T, H, 72)
+    want = oracle.all_to_all(send_np, topk, E)
+    send = [to_dev(a.reshape(-1)).view(T, H) for a in send_np]
+    for place in ("linear", "xcd"):
+        recv = [torch.zeros((max(rows), H), dtype=torch.bfloat16, device="cuda") for _ in range(P)]
+        nuna.all_to_all(send, recv, lay, placement=place)
+        out = [torch.zeros((T, H), dtype=torch.bfloat16, device="cuda") for _ in range(P)]
+        nuna.all_to_all_combine(recv, out, lay, placement=place)
+        torch.cuda.synchronize()
+        for d in range(P):
+            assert_bitwise(to_host(recv[d])[:rows[d]], want[d], f"dispatch {place} rank {d}")
+        back = oracle.combine(want, topk, E, None)
+        for s in range(P):
+            assert_bitwise(to_host(out[s]), back[s], f"combine {place} rank {s}")
+    lay.close()
