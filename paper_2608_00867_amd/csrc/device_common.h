@@ -134,13 +134,8 @@ __device__ __forceinline__ uint4 load16(const uint4* p) {
 // global_load_dwordx4 (global memory takes any alignment on this hardware).
 typedef unsigned int u32x4_any_t __attribute__((ext_vector_type(4), aligned(2)));
 
-template <bool NT>
 __device__ __forceinline__ uint4 load16_any(const char* p) {
-    u32x4_any_t t;
-    if constexpr (NT)
-        t = __builtin_nontemporal_load(reinterpret_cast<const u32x4_any_t*>(p));
-    else
-        t = *reinterpret_cast<const u32x4_any_t*>(p);
+    const u32x4_any_t t = *reinterpret_cast<const u32x4_any_t*>(p);
     return make_uint4(t.x, t.y, t.z, t.w);
 }
 

@@ -510,22 +510,22 @@ void launch_ar_p(const void* const* in, void* const* out, int P, const ArShape& 
             case 8: launch_ar_8<DT, 8>(in, out, s, pl, G, nt, wt, st); break;
             default: break;  // refused by launch_allreduce
         }
-        return;
-    }
-    switch (P) {
-        case 2: launch_ar_t<2, 2, DT, VPT>(in, out, P, s, pl, G, nt, st); break;
-        case 4: launch_ar_t<4, 4, DT, VPT>(in, out, P, s, pl, G, nt, st); break;
-        case 8: launch_ar_8<DT, VPT>(in, out, s, pl, G, nt, wt, st); break;
-        case 16: launch_ar_t<16, 16, DT, VPT>(in, out, P, s, pl, G, nt, st); break;
-        default:
-            if constexpr (VPT == 1) {
-                if (P == 32) launch_ar_t<32, 64, DT, 1>(in, out, P, s, pl, G, nt, st);
-                else if (P == 64) launch_ar_t<64, 64, DT, 1>(in, out, P, s, pl, G, nt, st);
-                else launch_ar_t<0, 64, DT, 1>(in, out, P, s, pl, G, nt, st);
-            } else {
-                launch_ar_t<0, 64, DT, VPT>(in, out, P, s, pl, G, nt, st);  // other P up to 16 (above: VPT 1)
-            }
-            break;
+    } else {
+        switch (P) {
+            case 2: launch_ar_t<2, 2, DT, VPT>(in, out, P, s, pl, G, nt, st); break;
+            case 4: launch_ar_t<4, 4, DT, VPT>(in, out, P, s, pl, G, nt, st); break;
+            case 8: launch_ar_8<DT, VPT>(in, out, s, pl, G, nt, wt, st); break;
+            case 16: launch_ar_t<16, 16, DT, VPT>(in, out, P, s, pl, G, nt, st); break;
+            default:
+                if constexpr (VPT == 1) {
+                    if (P == 32) launch_ar_t<32, 64, DT, 1>(in, out, P, s, pl, G, nt, st);
+                    else if (P == 64) launch_ar_t<64, 64, DT, 1>(in, out, P, s, pl, G, nt, st);
+                    else launch_ar_t<0, 64, DT, 1>(in, out, P, s, pl, G, nt, st);
+                } else {
+                    launch_ar_t<0, 64, DT, VPT>(in, out, P, s, pl, G, nt, st);  // other P up to 16 (above: VPT 1)
+                }
+                break;
+        }
     }
 }
 

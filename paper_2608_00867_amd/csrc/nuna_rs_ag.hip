@@ -160,7 +160,7 @@ __device__ __forceinline__ void reduce_ranks_any(const Ptrs<MAXP>& p, const Rank
                 for (int j = 0; j < VPT; ++j) {
                     int64_t v = v0 + j * nt;
                     if (!FULL) v = v < 0 ? 0 : v < limit ? v : limit - 1;
-                    buf[q][j] = load16_any<false>(src + v * 16);
+                    buf[q][j] = load16_any(src + v * 16);
                 }
             }
         // Loads first: the scheduler otherwise runs the ranks of a partial chunk one after another
@@ -485,7 +485,7 @@ __global__ __launch_bounds__(kWG) void k_all_gather_ragged(Ptrs<MAXP> p, int64_t
             uint4 y[VPT];
             if (c * cv >= k.lead && (c + 1) * cv - k.lead <= k.nv) {
 #pragma unroll
-                for (int j = 0; j < VPT; ++j) y[j] = load16_any<false>(from + (v0 + j * nt) * 16);
+                for (int j = 0; j < VPT; ++j) y[j] = load16_any(from + (v0 + j * nt) * 16);
                 each_destination([&](char* out) {
                     char* dst = out + base;
                     if (dst != src)  // else an in-place shard
@@ -494,7 +494,7 @@ __global__ __launch_bounds__(kWG) void k_all_gather_ragged(Ptrs<MAXP> p, int64_t
             } else {
 #pragma unroll
                 for (int j = 0; j < VPT; ++j)
-                    if (v0 + j * nt >= 0 && v0 + j * nt < k.nv) y[j] = load16_any<false>(from + (v0 + j * nt) * 16);
+                    if (v0 + j * nt >= 0 && v0 + j * nt < k.nv) y[j] = load16_any(from + (v0 + j * nt) * 16);
                 each_destination([&](char* out) {
                     char* dst = out + base;
                     if (dst != src)
@@ -702,11 +702,15 @@ template <int PT>
 void launch_ag_direct_p(const void* const* in, void* const* out, const AgShape& s, int vpt, bool cached, bool wt,
                         dim3 g, dim3 b, hipStream_t st) {
     const auto p = make_ptrs<rank_cap<PT>()>(in, out, s.P, s.P);
-    if (cached && wt && PT == 8) {
-        if (vpt == 4) hipLaunchKernelGGL((k_all_gather_direct<PT, 4, true, true>), g, b, 0, st, p, s.mv, s.gap, s.P);
-        else if (vpt == 2) hipLaunchKernelGGL((k_all_gather_direct<PT, 2, true, true>), g, b, 0, st, p, s.mv, s.gap, s.P);
-        else hipLaunchKernelGGL((k_all_gather_direct<PT, 1, true, true>), g, b, 0, st, p, s.mv, s.gap, s.P);
-    } else if (cached) {
+    if constexpr (PT == 8) {
+        if (cached && wt) {
+            if (vpt == 4) hipLaunchKernelGGL((k_all_gather_direct<PT, 4, true, true>), g, b, 0, st, p, s.mv, s.gap, s.P);
+            else if (vpt == 2) hipLaunchKernelGGL((k_all_gather_direct<PT, 2, true, true>), g, b, 0, st, p, s.mv, s.gap, s.P);
+            else hipLaunchKernelGGL((k_all_gather_direct<PT, 1, true, true>), g, b, 0, st, p, s.mv, s.gap, s.P);
+            return;
+        }
+    }
+    if (cached) {
         if (vpt == 4) hipLaunchKernelGGL((k_all_gather_direct<PT, 4, true, false>), g, b, 0, st, p, s.mv, s.gap, s.P);
         else if (vpt == 2) hipLaunchKernelGGL((k_all_gather_direct<PT, 2, true, false>), g, b, 0, st, p, s.mv, s.gap, s.P);
         else hipLaunchKernelGGL((k_all_gather_direct<PT, 1, true, false>), g, b, 0, st, p, s.mv, s.gap, s.P);

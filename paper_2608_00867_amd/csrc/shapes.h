@@ -7,6 +7,8 @@
 
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "device_common.h"
 
 namespace nuna {
@@ -382,17 +384,12 @@ inline int pick_row_threads(int64_t rowvec, bool capped) {
 
 constexpr int kRowVpt = 4;
 
-template <int N>
-struct IntTag {
-    static constexpr int value = N;
-};
-
 // Calls f with the threads of a row copy as a compile-time constant.
 template <typename F>
 inline void with_row_threads(int nt, F&& f) {
-    if (nt == 64) f(IntTag<64>{});
-    else if (nt == 128) f(IntTag<128>{});
-    else f(IntTag<kWG>{});
+    if (nt == 64) f(std::integral_constant<int, 64>{});
+    else if (nt == 128) f(std::integral_constant<int, 128>{});
+    else f(std::integral_constant<int, kWG>{});
 }
 
 }  // namespace
