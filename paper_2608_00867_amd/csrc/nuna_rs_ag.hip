@@ -109,8 +109,9 @@ __global__ __launch_bounds__(kWG) void k_reduce_scatter_direct(Ptrs<rank_cap<PT>
 // are moved element by element by one more workgroup per shard, so that no
 // chunk waits for them.
 // An element per thread with a 64-bit division for its shard, which now serves
-// the small shards only (below), took 15.4 us for the reduce-scatter of 8 ranks of bf16 at 512 KiB shards (now
-// 8.0) and 55.1 us for the all-gather at 2 MiB shards (24.2).
+// small shards only (below), took 15.4 us for the reduce-scatter of 8 ranks of
+// bf16 at 512 KiB shards (now 8.0) and 55.1 us for the all-gather at 2 MiB shards
+// (24.2).
 constexpr int kLineVecs = 8;  // 16-byte vectors in a 128-byte line
 
 struct RaggedCut {

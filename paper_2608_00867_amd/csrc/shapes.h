@@ -86,9 +86,10 @@ inline DirectMap direct_map(int mode, int64_t items, int64_t chunk_bytes) {
 }
 
 // Vectors per thread per work item for the all-reduce and reduce-scatter with
-// up to 16 ranks, by message size (measured on MI355X with bf16, cold): 4 at
-// 4 MiB per rank, 2 at 16 MiB, 1 at 64 MiB and above and for every smaller
-// (latency-bound) message, where more workgroups win.
+// up to 16 ranks, by message size, where no row below says otherwise (measured on
+// MI355X with bf16, cold, among 256-thread shapes): 4 at 4 MiB per rank, 2 at
+// 16 MiB, 1 at 64 MiB and above and for every smaller (latency-bound) message,
+// where more workgroups win.
 inline int pick_vpt(int64_t vectors_per_rank, int P) {
     if (P > 16) return 1;
     const int forced = tuning().vpt;
@@ -128,8 +129,9 @@ inline int largest_divisor_upto(int P, int cap) {
 
 // Workgroup size: one-wavefront workgroups spread small messages, and the
 // long per-thread rank loops of many-rank reductions, over more compute
-// units; 256-thread workgroups stream large few-rank messages, except at
-// 4 MiB per rank where 128 threads with 4 vectors each measured best.
+// units; 256-thread workgroups stream large few-rank messages, except from
+// 4 MiB per rank, where 128 threads with 4 vectors each measured better than 256
+// (the rows below replace both where they were better still).
 inline int pick_threads(int64_t vectors_per_rank, int P) {
     const int forced = tuning().wg_threads;
     if (forced == 64 || forced == 128 || forced == 256) return forced;
