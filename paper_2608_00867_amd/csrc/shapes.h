@@ -304,7 +304,8 @@ inline void shared_ar_shape(int64_t vectors_per_rank, int P, int& nt, int& vpt) 
 // run-time count:
 //   3 ranks        3 MiB 4.33 -> 3.92 (64x4)
 //   5-7 ranks      1.5 MiB 4.1-5.0 -> 3.6-4.7 (64x1; with fp32 from 1.1 to 2.8 MiB, where 256x1 is
-//                  the slower one: 7 ranks at 1.2 MiB 4.2 and 3.4), 8 MiB 15.4-22.9 -> 15.0-21.2 (256x4)
+//                  the slower one: 7 ranks at 1.2 MiB 4.2 and 3.4; those past 2.5 MiB, where 64x1 begins
+//                  another round, 128x2: 2.75 MiB 6.6 against 7.0), 8 MiB 15.4-22.9 -> 15.0-21.2 (256x4)
 //   9-15 ranks     3 MiB 14.3 -> 12.9 (128x2), 6 MiB 30.8 -> 27.2 (128x2); with fp32 at 6.5-7.5 MiB the
 //                  shared 128x4 (26.4-35 against 27.6-36) and past 8 MiB, two rounds of 256x4, too
 // The 8-rank 256x8 is taken when its rounds are at least 80 % full, from 16 MiB
@@ -325,7 +326,8 @@ inline void pick_ar_shape(int64_t vectors_per_rank, int P, int dtype, int& nt, i
     static constexpr ShapeRow k16b[] = {{5, 256, 2}, {8.05f, 0, 0}, {9, 64, 2}, {13, 64, 4}, {15, 0, 0},
                                         {20, 128, 2}, {26, 0, 0}, {34, 128, 2}, {64, 0, 0}};
     static constexpr ShapeRow k3[] = {{10, 64, 4}, {14, 0, 0}};
-    static constexpr ShapeRow k7f[] = {{4.5f, 64, 1}, {11.5f, 0, 0}, {28, 256, 4}, {56, 0, 0}};
+    static constexpr ShapeRow k6f[] = {{4.5f, 64, 1}, {11.5f, 0, 0}, {28, 256, 4}, {56, 0, 0}};
+    static constexpr ShapeRow k7f[] = {{4.5f, 64, 1}, {10.05f, 128, 2}, {13.2f, 0, 0}, {28, 256, 4}, {56, 0, 0}};
     static constexpr ShapeRow k7b[] = {{5, 64, 1}, {7, 0, 0}, {28, 256, 4}, {56, 0, 0}};
     static constexpr ShapeRow k15f[] = {{10, 128, 2}, {14, 0, 0}, {18, 128, 2}, {26, 0, 0}, {30, 256, 4},
                                         {32.05f, 0, 0}, {38, 128, 2}, {56, 0, 0}};
@@ -335,7 +337,9 @@ inline void pick_ar_shape(int64_t vectors_per_rank, int P, int dtype, int& nt, i
     if (P == 2) f32 ? row_shape(k2f, v, nt, vpt) : row_shape(k2b, v, nt, vpt);
     else if (P == 3) row_shape(k3, v, nt, vpt);
     else if (P == 4) f32 ? row_shape(k4f, v, nt, vpt) : row_shape(k4b, v, nt, vpt);
-    else if (P >= 5 && P <= 7) f32 ? row_shape(k7f, v, nt, vpt) : row_shape(k7b, v, nt, vpt);
+    else if (P >= 5 && P <= 7 && !f32) row_shape(k7b, v, nt, vpt);
+    else if (P == 7) row_shape(k7f, v, nt, vpt);
+    else if (P >= 5 && P <= 6) row_shape(k6f, v, nt, vpt);
     else if (P == 8) f32 ? row_shape(k8f, v, nt, vpt) : row_shape(k8b, v, nt, vpt);
     else if (P >= 9 && P <= 15) f32 ? row_shape(k15f, v, nt, vpt) : row_shape(k15b, v, nt, vpt);
     else if (P == 16) f32 ? row_shape(k16f, v, nt, vpt) : row_shape(k16b, v, nt, vpt);

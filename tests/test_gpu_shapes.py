@@ -226,8 +226,10 @@ def test_two_shot_of_two_kernels_at_2_to_4_mib(nuna, P, n):
                                                     (16, "f32", 8.2, (256, 1)), (16, "f32", 9, (64, 4)),
                                                     (11, "f32", 26, (128, 4)), (11, "f32", 32, (256, 4)),
                                                     (11, "f32", 33, (128, 4)), (11, "bf16", 26, (128, 2)),
-                                                    (7, "f32", 4.6, (64, 1)), (7, "f32", 11, (64, 1)),
-                                                    (7, "f32", 12, (256, 1)), (7, "bf16", 8, (256, 1)),
+                                                    (7, "f32", 4.6, (64, 1)), (6, "f32", 11, (64, 1)),
+                                                    (7, "f32", 10, (64, 1)), (7, "f32", 11, (128, 2)),
+                                                    (7, "f32", 13.5, (256, 1)), (6, "f32", 12, (256, 1)),
+                                                    (7, "bf16", 8, (256, 1)),
                                                     (2, "bf16", 13, (256, 1)), (2, "bf16", 15, (64, 8))])
 def test_one_shot_rows(nuna, P, dtype, quarters, shape):
     n = int(quarters * (1 << 18)) // ES[dtype] // 64 * 64 + 3
