@@ -657,7 +657,7 @@ hipError_t launch_reduce_scatter(const void* const* in, void* const* out, int P,
             return hipGetLastError();
         }
         int nt, vpt;
-        pick_rs_shape(mv * P, P, dtype, nt, vpt);
+        pick_rs_shape(mv * P, P, dtype, false, nt, vpt);
         if (P > 16) vpt = 1;
         if (vpt == 1 && !tuning().wg_threads) nt = 64;  // more workgroups for the small sizes
         const int64_t cv = static_cast<int64_t>(nt) * vpt;
@@ -673,7 +673,7 @@ hipError_t launch_reduce_scatter(const void* const* in, void* const* out, int P,
     s.P = P;
     // Shape by the vectors each input rank holds (P shards of mv vectors).
     int nt, vpt;
-    pick_rs_shape(s.mv * P, P, dtype, nt, vpt);
+    pick_rs_shape(s.mv * P, P, dtype, !keep_output, nt, vpt);
     const int64_t row_cv = static_cast<int64_t>(nt) * vpt;
     if (grid_capped((s.mv + row_cv - 1) / row_cv * P)) {
         pick_rs_capped_shape(s.mv * P, P, dtype, nt, vpt);

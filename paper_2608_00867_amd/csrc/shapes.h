@@ -181,8 +181,12 @@ void row_shape(const ShapeRow (&rows)[N], int64_t vectors, int& nt, int& vpt) {
 //   4 ranks   1 MiB 2.21 -> 1.96 (64x1), 8 MiB f32 8.8 -> 7.2 (64x4), 11 MiB f32 11.8 -> 10.4 (256x4)
 //   12 ranks  512 KiB 3.5 -> 3.1 (64x1), 16 MiB bf16 46.9 -> 41.2 (256x2)
 //   16 ranks  2 MiB 7.4 -> 6.6 (256x2), 4 MiB f32 15.0 -> 12.1 (256x4), 8 MiB f32 27.2 -> 25.7 (256x4)
-// Forced tunables win.
-inline void pick_rs_shape(int64_t in_vectors, int P, int dtype, int& nt, int& vpt) {
+// 8 ranks of fp32 keep 64x1 at 4.4-5.5 MiB in a call of their own (`alone`: whole
+// vectors, no all-gather after it): at 4.75 MiB 8.2 with 128x1, 8.2 with 64x4 and
+// 7.85 with 64x1, at 5 MiB 8.4, 8.5 and 8.2.  The two-shot's phase (5-10 % slower
+// with it, chunk for chunk as its all-gather cuts) and ragged shards (8.3 -> 9.1
+// at 4.75 MiB) take 64x4 throughout.  Forced tunables win.
+inline void pick_rs_shape(int64_t in_vectors, int P, int dtype, bool alone, int& nt, int& vpt) {
     nt = pick_threads(in_vectors, P);
     vpt = dtype == kDtBf16 || tuning().vpt ? pick_vpt(in_vectors, P) : 1;
     if (P > 16 || tuning().wg_threads || tuning().vpt) return;
@@ -191,6 +195,7 @@ inline void pick_rs_shape(int64_t in_vectors, int P, int dtype, int& nt, int& vp
     static constexpr ShapeRow k4[] = {{3, 64, 1}, {7, 0, 0}, {16, 64, 4}, {32, 256, 4}};
     static constexpr ShapeRow k7[] = {{2, 64, 1}, {15, 128, 2}, {32, 256, 4}};
     static constexpr ShapeRow k8[] = {{1, 64, 1}, {7, 0, 0}, {16, 64, 4}, {32, 256, 4}};
+    static constexpr ShapeRow k8f[] = {{17.5f, 64, 1}, {22.05f, 0, 0}};
     static constexpr ShapeRow k15[] = {{1, 64, 1}, {7, 0, 0}, {16, 128, 2}, {18, 256, 2}, {30, 128, 2},
                                        {40, 256, 2}};
     static constexpr ShapeRow k16[] = {{2, 128, 1}, {3, 0, 0}, {5, 256, 2}, {10, 128, 2}, {14, 256, 4}, {18, 256, 2},
@@ -201,6 +206,7 @@ inline void pick_rs_shape(int64_t in_vectors, int P, int dtype, int& nt, int& vp
     else if (P == 8) row_shape(k8, in_vectors, nt, vpt);
     else if (P <= 15) row_shape(k15, in_vectors, nt, vpt);
     else row_shape(k16, in_vectors, nt, vpt);
+    if (alone && P == 8 && dtype == kDtF32) row_shape(k8f, in_vectors, nt, vpt);
 }
 
 // Reduce-scatter under a workgroup cap: 256 threads, fp32 with 1 vector per

@@ -237,6 +237,23 @@ def test_one_shot_rows(nuna, P, dtype, quarters, shape):
     assert (rec["threads"], rec["vectors_per_thread"]) == shape, rec
 
 
+@pytest.mark.parametrize("quarters,extra,shape", [(17, 0, (64, 4)), (18, 0, (64, 1)), (20, 0, (64, 1)), (20, 1, (64, 4)),
+                                                  (22, 0, (64, 1)), (23, 0, (64, 4))])
+def test_reduce_scatter_rows_of_fp32(nuna, quarters, extra, shape):
+    """8 ranks of fp32 at 4.25 to 5.75 MiB of input: a call of whole vectors, ragged shards, and the phase of the
+    two kernels, whose chunk stays the all-gather's."""
+    m = quarters * 65536 // 8 + extra
+    x = _values(8, 8 * m, "f32", quarters)
+    ref = oracle.reduce_scatter(x)
+    outs = nuna.reduce_scatter([to_dev(a) for a in x])
+    rec = nuna.last_launch()
+    assert (rec["threads"], rec["vectors_per_thread"]) == shape, rec
+    torch.cuda.synchronize()
+    for d in (0, 7):
+        assert_bitwise(to_host(outs[d]), ref[d], f"{quarters} quarters + {extra} shard {d}")
+    _allreduce(nuna, 8, "f32", 8 * (m & ~3), f"two kernels {quarters}", algo="two_shot_two_kernels")
+
+
 # ---------------------------------------------------------------- tunables
 
 def test_many_rank_tunable_says_from_where(nuna):
