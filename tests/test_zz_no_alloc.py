@@ -112,8 +112,8 @@ def test_routed_launch_record_names_the_map(nuna):
 
 @pytest.mark.parametrize("grid", [7, 24])
 def test_routed_capped_grid_runs_several_items_per_workgroup(nuna, grid):
-    """A capped grid hands every workgroup many (token, slot) items: the decode kernel's per-item counts
-    alternate between two LDS buffers, and the copy kernel's prefix is reused across items.  7 workgroups
+    """A capped grid hands every workgroup many (token, slot) items: the decode kernel's masks and
+    the copy kernel's prefix, both formed once per workgroup, serve all of them.  7 workgroups
     run the linear map, 24 the XCD map."""
     with nuna.tunables(NUNA_MAX_GRID=grid):
         _check_case(nuna, 8, 30, 8, 256, 72, 61, "xcd")
